@@ -44,7 +44,13 @@ struct EvalPlan {
     int32_t n_pg;     // pair groups per run
     int64_t bc;       // blocks per chunk
     int64_t nchunks;  // chunks per member
+    bool folded;      // even and odd sums of a pair (k_eval_fold) instead of its two members
 };
+// Runs of more pair-blocks (P nb) than this have an evaluate plan of their own:
+// none of them fits the fused loop's or the grid loop's LDS (at most 147,456
+// stored normals' blocks in 16 x 144 KB), so their sums need not follow the
+// loops' order.
+constexpr int64_t EVAL_LARGE_FROM = 1 << 18;
 EvalPlan eval_plan(const Geometry& g, int64_t bc_override);
 int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e);  // floats
 

@@ -385,6 +385,235 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same evaluate for runs of many pair-blocks (EvalPlan::folded), antithetic
+// sampling only.  A pair's members are m + b and m - b with one b = sigma (.)
+// eps, so each problem term splits into a part that is even in b, the same for
+// both members, and a part that is odd in b, which changes sign:
+//   sphere      (a +- b)^2, a = m - s: a^2 + b^2 and 2ab.  With a scalar
+//               sigma the sum of b^2 over a Box-Muller pair is sigma^2 r^2 =
+//               -2 ln2 sigma^2 log2 u (cos^2 + sin^2 = 1), and the products
+//               are r (cos a_0 + sin a_1): no normal is formed at all;
+//   Rastrigin   m^2 + b^2 - A cos(2 pi m) cos(2 pi b), 2mb + A sin(2 pi m) sin(2 pi b);
+//   Rosenbrock  100 q^2 with q = E +- O, E = m_n - m^2 - b^2, O = b_n - 2mb:
+//               100 (E^2 + O^2) and 200 EO; (1 - m -+ b)^2 as the sphere.
+// What depends on the dim alone (a, cos 2 pi m, ...) is made once per
+// workgroup into LDS and read as broadcasts, so the loop spends its VALU
+// instructions on one even and one odd sum instead of on two members: per
+// Philox block 79 -> 58 (shifted sphere), 109 -> 82 (Rastrigin).  The kernel
+// is bound by their number.
+//
+// The sums are fp32 over EVAL_FOLD blocks folded into fp64; the members'
+// values even + odd, even - odd are formed in fp64.  Where a lane's odd sum
+// comes near its even one (a member near a zero of f: the difference would
+// lose digits) or the sums leave the range that squares of fp32 values have
+// room in, the lane's chunk is evaluated member by member instead, with
+// eval_chunk: the results keep their precision, infinities and NaN.
+constexpr double SQRT_2LN2 = 1.17741002251547469101;  // sqrt(2 ln 2); its fp32 rounding would bias every b by 1.4e-8
+constexpr double TWO_LN2 = 1.38629436111989061883;
+constexpr int FOLD_TILE_MIN = 256;  // dims staged at once, at least (else one per lane)
+
+template <int PROB, int SM>
+struct FoldRows {
+    static constexpr bool sphere = PROB == ES_PROB_SPHERE || PROB == ES_PROB_SHIFTED_SPHERE;
+    static constexpr int terms = sphere ? 1 : 3;
+    static constexpr int n = terms + (SM == SM_VEC ? 1 : 0);  // float rows of one tile, then a quarter row of block sums
+};
+
+constexpr int fold_tile(int wg) { return wg > FOLD_TILE_MIN ? wg : FOLD_TILE_MIN; }
+
+// What dim d contributes to the even sum by itself goes to q; t: its rows.
+// Rosenbrock: the term of dims d - 1 and d (d >= 1), scaled by 1 / 100.
+template <int PROB, int SM>
+__device__ __forceinline__ void fold_rows(const float* __restrict__ mr, const float* __restrict__ pdata, int64_t d,
+                                          float ra, float t[3], float& q)
+{
+    const float m = mr[d];
+    if constexpr (FoldRows<PROB, SM>::sphere) {
+        const float a = PROB == ES_PROB_SHIFTED_SPHERE ? m - pdata[d] : m;
+        t[0] = SM == SM_VEC ? 2.0f * a : a;
+        q = a * a;
+    } else if constexpr (PROB == ES_PROB_RASTRIGIN) {
+        float sn, cs;
+        sincospif(2.0f * (m - rintf(m)), &sn, &cs);  // m - rint m is exact
+        t[0] = 2.0f * m;
+        t[1] = -ra * cs;
+        t[2] = ra * sn;
+        q = m * m;
+    } else {
+        const float mi = mr[d - 1], o = 1.0f - mi;
+        t[0] = fmaf(-mi, mi, m);
+        t[1] = -2.0f * mi;
+        t[2] = -0.01f * o;
+        q = 0.01f * o * o;
+    }
+}
+
+// Even and odd sums of one Philox block (words w).  tr: the rows' values of
+// its four dims; ss: sigma sqrt(2 ln 2) (scalar sigma; VEC: the last row has
+// each dim's); kb: -2 ln2 sigma^2 (times 1 / 100 for Rosenbrock); bl:
+// Rosenbrock's b of the dim before the block.  Even parts that are small where
+// sigma is (b^2, O^2) have a sum of their own: added one by one to a sum that
+// holds E^2 or A cos, with most of them below its last place, they would
+// round down on average.
+template <int PROB, int SM>
+__device__ __forceinline__ void fold_block(uint4 w, const float (&tr)[FoldRows<PROB, SM>::n][4], float ss, float kb,
+                                           float& bl, float& even, float& small, float& odd)
+{
+    const uint32_t wr[2] = {w.x, w.z}, wa[2] = {w.y, w.w};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float l = __builtin_amdgcn_logf(__builtin_fmaf(word24(wr[h]), WORD24_SCALE, 0x1p-24f));
+        const float r = __builtin_amdgcn_sqrtf(-l), th = bm_turns(wa[h]);
+        const float cs[2] = {__builtin_amdgcn_cosf(th), __builtin_amdgcn_sinf(th)};
+        if constexpr (FoldRows<PROB, SM>::sphere && SM == SM_SCALAR) {
+            // in units of kb (even) and 2 sigma sqrt(2 ln 2) (odd)
+            small += l;
+            odd = fmaf(r, fmaf(cs[0], tr[0][2 * h], cs[1] * tr[0][2 * h + 1]), odd);
+            continue;
+        }
+        const float sr = SM == SM_SCALAR ? ss * r : r;
+        if constexpr (SM == SM_SCALAR) small = fmaf(l, kb, small);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = 2 * h + i;
+            const float b = SM == SM_SCALAR ? sr * cs[i] : tr[FoldRows<PROB, SM>::terms][k] * (r * cs[i]);
+            if constexpr (FoldRows<PROB, SM>::sphere) {
+                small = fmaf(b, b, small);
+                odd = fmaf(b, tr[0][k], odd);
+            } else if constexpr (PROB == ES_PROB_RASTRIGIN) {
+                if constexpr (SM == SM_VEC) small = fmaf(b, b, small);
+                const float f = __builtin_amdgcn_fractf(b);
+                even = fmaf(__builtin_amdgcn_cosf(f), tr[1][k], even);
+                odd = fmaf(__builtin_amdgcn_sinf(f), tr[2][k], odd);
+                odd = fmaf(b, tr[0][k], odd);
+            } else {
+                if constexpr (SM == SM_VEC) small = fmaf(b * 0.01f, b, small);
+                const float E = fmaf(-bl, bl, tr[0][k]), O = fmaf(tr[1][k], bl, b);
+                even = fmaf(E, E, even);
+                small = fmaf(O, O, small);
+                odd = fmaf(E, O, odd);
+                odd = fmaf(bl, tr[2][k], odd);
+                bl = b;
+            }
+        }
+    }
+}
+
+template <int PROB, int SM>
+__global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_eval_fold(
+    const float* __restrict__ m, const float* __restrict__ pdata, float* __restrict__ partial,
+    uint64_t seed, uint32_t t, int64_t D, int64_t nb, int32_t N, int32_t P, int64_t bc, int64_t nchunks,
+    int32_t n_pg, const float* __restrict__ hp, float ra, const float* __restrict__ svec)
+{
+    using FR = FoldRows<PROB, SM>;
+    extern __shared__ __align__(16) float rows[];  // [FR::n][TD] | block sums [TD / 4]
+    const int32_t r = blockIdx.y;
+    const float sigma = hp[r];
+    const uint32_t w = blockIdx.x;
+    const uint32_t slot = w >> 3, xcd = w & 7u;
+    const int32_t pg = (int32_t)(slot % (uint32_t)n_pg);
+    const int64_t chunk = (int64_t)(slot / (uint32_t)n_pg) * 8 + xcd;
+    if (chunk >= nchunks) return;
+    const int32_t p = pg * (int32_t)blockDim.x + (int32_t)threadIdx.x;
+    const uint32_t row = (uint32_t)(p < P ? p : P - 1);
+    const uint64_t key = seed + (uint64_t)r;
+    const uint32_t k0 = (uint32_t)key, k1 = (uint32_t)(key >> 32);
+    const int64_t b0 = chunk * bc;
+    const int64_t b1 = b0 + bc < nb ? b0 + bc : nb;
+    const float* __restrict__ mr = m + (int64_t)r * 4 * nb;
+    const float* __restrict__ gr = SM == SM_VEC ? svec + (int64_t)r * 4 * nb : nullptr;
+    // folded: the whole groups of EVAL_FOLD full blocks (Rosenbrock: without
+    // the row's first group, whose first dim has none before it)
+    const int64_t nfull = D / 4 < b1 ? D / 4 : b1;
+    const int64_t f0 = PROB == ES_PROB_ROSENBROCK && b0 == 0 ? EVAL_FOLD : b0;
+    const int64_t f1 = nfull > f0 ? f0 + (nfull - f0) / EVAL_FOLD * EVAL_FOLD : f0;
+    const int32_t wg = (int32_t)blockDim.x, TD = fold_tile(wg);
+
+    const double kbd = -TWO_LN2 * (double)sigma * (double)sigma;
+    const float kb = (float)(PROB == ES_PROB_ROSENBROCK ? 0.01 * kbd : kbd);
+    // the sphere's even sums are kept in units of kb: sum of log2 u plus the
+    // dims' own squares times 1 / kb
+    const double qs = FR::sphere && SM == SM_SCALAR ? 1.0 / kbd : 1.0;
+    const float ss = (float)(SQRT_2LN2 * (double)sigma);
+    float bl = 0.f;
+    if (PROB == ES_PROB_ROSENBROCK && f1 > f0) {
+        float e[4];
+        box_muller4(philox4x32_10<LANES_ROW>(k0, k1, (uint32_t)(f0 - 1), row, t, DOM_NOISE), e);
+        bl = (SM == SM_VEC ? gr[4 * f0 - 1] : sigma) * e[3];
+    }
+    double even = PROB == ES_PROB_ROSENBROCK ? 0.01 * (double)bl * (double)bl : 0.0, odd = 0.0;
+    for (int64_t bt = f0; bt < f1; bt += TD / 4) {
+        const int32_t nbt = (int32_t)(f1 - bt < TD / 4 ? f1 - bt : TD / 4);
+        if (bt > f0) __syncthreads();  // every lane is done with the previous tile
+        for (int32_t i = (int32_t)threadIdx.x; i < 4 * nbt; i += wg) {
+            float tv[3] = {0.f, 0.f, 0.f}, q;
+            fold_rows<PROB, SM>(mr, pdata, 4 * bt + i, ra, tv, q);
+#pragma unroll
+            for (int k = 0; k < FR::terms; ++k) rows[k * TD + i] = tv[k];
+            if constexpr (SM == SM_VEC) rows[FR::terms * TD + i] = (float)(SQRT_2LN2 * (double)gr[4 * bt + i]);
+            // the block's own sum: its four dims are neighbouring lanes
+            q += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(q), 0xB1, 0xF, 0xF, false));
+            q += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(q), 0x4E, 0xF, 0xF, false));
+            if ((i & 3) == 0) rows[FR::n * TD + (i >> 2)] = (float)((double)q * qs);
+        }
+        __syncthreads();
+        for (int32_t i = 0; i < nbt; i += EVAL_FOLD) {
+            const float4 q4 = *reinterpret_cast<const float4*>(rows + FR::n * TD + i);
+            float ev = (q4.x + q4.y) + (q4.z + q4.w), es = 0.f, od = 0.f;
+#pragma unroll
+            for (int k = 0; k < EVAL_FOLD; ++k) {
+                float tr[FR::n][4];
+#pragma unroll
+                for (int j = 0; j < FR::n; ++j) {
+                    const float4 v = *reinterpret_cast<const float4*>(rows + j * TD + 4 * (i + k));
+                    tr[j][0] = v.x; tr[j][1] = v.y; tr[j][2] = v.z; tr[j][3] = v.w;
+                }
+                fold_block<PROB, SM>(philox4x32_10<LANES_ROW>(k0, k1, (uint32_t)(bt + i + k), row, t, DOM_NOISE), tr,
+                                     ss, kb, bl, ev, es, od);
+            }
+            even += (double)(ev + es);
+            odd += (double)od;
+        }
+    }
+    double span;  // what the odd sum is measured against
+    if constexpr (FR::sphere) {
+        if constexpr (SM == SM_SCALAR) {
+            even *= kbd;
+            odd *= 2.0 * SQRT_2LN2 * (double)sigma;
+        }
+        span = even;
+    } else if constexpr (PROB == ES_PROB_RASTRIGIN) {
+        span = even + 8.0 * (double)(f1 - f0) * fabs((double)ra);  // 2 |A| per dim
+    } else {
+        even = 100.0 * (even - 0.01 * (double)bl * (double)bl);
+        odd *= 200.0;
+        span = even;
+    }
+    double accp = even + odd, accm = even - odd;
+    const bool whole = fabs(odd) <= 0.9375 * span && span < 1e30;
+    // member by member: the folded blocks of a lane that needs it, then the
+    // blocks before and after them
+    for (int part = 0; part < 3; ++part) {
+        const int64_t c0 = part == 0 ? f0 : part == 1 ? b0 : f1, c1 = part == 0 ? f1 : part == 1 ? (f0 < b1 ? f0 : b1) : b1;
+        if (c1 <= c0 || (part == 0 && __all(whole))) continue;
+        double dp, dm;
+        eval_chunk<PROB, LANES_ROW, SM>(mr, pdata, k0, k1, row, t, c0, c1, D, sigma, ra, dp, dm, gr);
+        if (part == 0) {
+            accp = whole ? accp : dp;
+            accm = whole ? accm : dm;
+        } else {
+            accp += dp;
+            accm += dm;
+        }
+    }
+    if (p < P) {
+        float* o = partial + (chunk * gridDim.y + r) * (int64_t)N;
+        o[p] = (float)accp;
+        o[p + P] = (float)accm;
+    }
+}
+
 // fit[r][j] = (add + sum over chunks (fixed order) of the partials) / div
 // (div = 1 for fitness, D for the weight-decay mean square).
 // Workgroup = 64 members x RED_SLICES chunk slices.
@@ -2211,12 +2440,52 @@ int grid_for(int64_t n, int threads)
 }  // namespace
 
 // ---------------------------------------------------------------------------
+// Blocks per evaluate chunk of a large run: the least estimated time over
+// whole groups of EVAL_FOLD blocks.  The estimate (us): the workgroups of the
+// fullest CU, at 0.1 us for four waves' block (58 instructions, one per four
+// cycles and SIMD) and more with few waves per SIMD, or one
+// wave's chain of blocks; and 4 ns per chunk for its start and its place in the
+// reduction's chain of loads.  Evaluate with its reduction in us, at 24576
+// waves (the smaller runs' plan) / at this rule's chunk: 40,528 dims x 1096
+// members 46 / 24, 200,000 x 64 57 / 20, 50,001 x 510 30 / 16, 100,001 x 510 x 2
+// runs 40 / 35, 250,003 x 1000 73 / 66, 3000 x 2048 x 3 15.3 / 12.7, 1e6 x 2048
+// 411 / 411.
+static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e)
+{
+    const int64_t per_chunk = (int64_t)e.n_pg * g.R;  // workgroups
+    const double waves = e.wg / 64;
+    int64_t best = EVAL_FOLD;
+    double least = 1e300;
+    for (int64_t bc = EVAL_FOLD;; bc += EVAL_FOLD * (1 + bc / (16 * EVAL_FOLD))) {
+        const int64_t nch = (g.nb + bc - 1) / bc;
+        const int64_t k = (nch * per_chunk + 255) / 256;  // workgroups on the fullest CU
+        const double per_simd = (double)k * waves / 4.0;
+        const double busy = 0.1 * per_simd * (double)bc * (1.0 + 0.4 / (per_simd < 8.0 ? per_simd : 8.0));
+        const double chain = 0.15 * (double)bc;
+        const double us = (busy > chain ? busy : chain) + 0.0042 * (double)nch;
+        if (us < least) {
+            least = us;
+            best = bc;
+        }
+        if (nch * per_chunk <= 64 || bc >= g.nb) break;
+    }
+    return best;
+}
+
 EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
 {
     EvalPlan e;
     const int32_t P64 = (g.P + 63) / 64 * 64;
     e.wg = P64 < EVAL_MAX_WG ? P64 : EVAL_MAX_WG;
     e.n_pg = (g.P + e.wg - 1) / e.wg;
+    const int64_t waves_per_chunk = (int64_t)e.n_pg * (e.wg / 64) * g.R;
+    const bool large = (int64_t)g.P * g.nb > EVAL_LARGE_FROM;
+    // Even and odd sums save VALU instructions and cost a staged tile per
+    // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, members /
+    // folded at their best chunks, shifted sphere: 36,000 12.7 / 14.1; 40,032
+    // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
+    // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
+    e.folded = large && g.P >= 2 && waves_per_chunk * g.nb >= (1 << 16);
     int64_t bc;
     if (bc_override > 0) {
         bc = bc_override;
@@ -2226,11 +2495,11 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
         // shorter workgroups of three rounds leave a shorter tail while the
         // last round drains than those of two (D = 1e6, N = 2048: evaluate
         // 536 -> 524 us; four rounds gain no more and add partials to sum).
-        const int64_t waves_per_chunk = (int64_t)e.n_pg * (e.wg / 64) * g.R;
         int64_t nch = (24576 + waves_per_chunk - 1) / waves_per_chunk;
         if (nch < 1) nch = 1;
         bc = (g.nb + nch - 1) / nch;
         if (bc < EVAL_FOLD) bc = EVAL_FOLD;
+        if (large) bc = eval_chunk_blocks(g, e);
         // a small run: chunks short enough that the fused loop's workgroup
         // takes every (pair, chunk) item at once
         if ((int64_t)g.P * g.nb <= (int64_t)FUSED_WG * EVAL_FOLD) {
@@ -2284,6 +2553,12 @@ hipError_t launch_ask(const Geometry& g, const es_config& c, uint32_t t, const f
     return hipGetLastError();
 }
 
+template <int PROB, int SM>
+constexpr uint32_t fold_lds_bytes(int wg)
+{
+    return (uint32_t)(sizeof(float) * (FoldRows<PROB, SM>::n * fold_tile(wg) + fold_tile(wg) / 4));
+}
+
 hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPlan& e, uint32_t t,
                             const float* m, const float* pdata, float* partial, float* fit,
                             const float* hp, const float* svec, double div, hipStream_t s, hipEvent_t ev_start,
@@ -2295,12 +2570,17 @@ hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPla
     const dim3 block((unsigned)e.wg);
     const int sm = c.strategy == ES_STRAT_SEP_CMA ? SM_INDEP : svec ? SM_VEC : SM_SCALAR;
     const float* sv = sm == SM_SCALAR ? nullptr : svec;
-#define ES_EVAL_LAUNCH(PROB, SM)                                                                                \
-    launch_timed(k_eval_bbob<PROB, SM>, grid, block, 0, s, ev_start, ev_stop, m, pdata, partial, c.seed, t, g.D, \
-                 g.nb, g.N, g.P, e.bc, e.nchunks, e.n_pg, hp, c.rastrigin_a, sv)
+#define ES_EVAL_ARGS                                                                                       \
+    m, pdata, partial, c.seed, t, g.D, g.nb, g.N, g.P, e.bc, e.nchunks, e.n_pg, hp, c.rastrigin_a, sv
+#define ES_EVAL_LAUNCH(PROB, SM) \
+    launch_timed(k_eval_bbob<PROB, SM>, grid, block, 0, s, ev_start, ev_stop, ES_EVAL_ARGS)
+#define ES_EVAL_PAIRS(PROB, SM)                                                                                  \
+    (e.folded ? launch_timed(k_eval_fold<PROB, SM>, grid, block, fold_lds_bytes<PROB, SM>(e.wg), s, ev_start, ev_stop, \
+                             ES_EVAL_ARGS)                                                                       \
+              : ES_EVAL_LAUNCH(PROB, SM))
 #define ES_EVAL_PROB(PROB)                                                                                      \
-    (sm == SM_INDEP ? ES_EVAL_LAUNCH(PROB, SM_INDEP) : sm == SM_VEC ? ES_EVAL_LAUNCH(PROB, SM_VEC)               \
-                                                                    : ES_EVAL_LAUNCH(PROB, SM_SCALAR))
+    (sm == SM_INDEP ? ES_EVAL_LAUNCH(PROB, SM_INDEP) : sm == SM_VEC ? ES_EVAL_PAIRS(PROB, SM_VEC)                \
+                                                                    : ES_EVAL_PAIRS(PROB, SM_SCALAR))
     hipError_t err;
     switch (c.problem) {
     case ES_PROB_SPHERE: err = ES_EVAL_PROB(ES_PROB_SPHERE); break;
@@ -2310,7 +2590,9 @@ hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPla
     default: return hipErrorInvalidValue;
     }
 #undef ES_EVAL_PROB
+#undef ES_EVAL_PAIRS
 #undef ES_EVAL_LAUNCH
+#undef ES_EVAL_ARGS
     if (err != hipSuccess) return err;
     const double add = c.problem == ES_PROB_RASTRIGIN ? (double)c.rastrigin_a * (double)g.D : 0.0;
     return launch_timed(k_eval_reduce, dim3((unsigned)((g.N + 63) / 64), (unsigned)g.R), dim3(64 * RED_SLICES), 0, s,
