@@ -112,6 +112,24 @@ __device__ __forceinline__ float bm_radius(uint32_t w)
 // Angle in revolutions, exact.
 __device__ __forceinline__ float bm_turns(uint32_t w) { return word24(w) * WORD24_SCALE; }
 
+// The same two pairs of normals in factors: r = sqrt(-log2 u), the radius in
+// units of sqrt(2 ln 2), and the cosine and sine; l = log2 u.  For sums that
+// apply that unit once at their end, in fp64.
+__device__ __forceinline__ void bm_factors(uint4 w, float l[2], float r[2], float cs[4])
+{
+    const uint32_t wr[2] = {w.x, w.z}, wa[2] = {w.y, w.w};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        l[h] = __builtin_amdgcn_logf(__builtin_fmaf(word24(wr[h]), WORD24_SCALE, 0x1p-24f));
+        r[h] = __builtin_amdgcn_sqrtf(-l[h]);
+        const float th = bm_turns(wa[h]);
+        cs[2 * h] = __builtin_amdgcn_cosf(th);
+        cs[2 * h + 1] = __builtin_amdgcn_sinf(th);
+    }
+}
+constexpr double TWO_LN2 = 1.38629436111989061883;
+constexpr double SQRT_2LN2 = 1.17741002251547469101;  // sqrt(2 ln 2); its fp32 rounding would bias every normal by 1.4e-8
+
 // Four standard normals from one Philox block.
 __device__ __forceinline__ void box_muller4(uint4 w, float e[4])
 {

@@ -409,8 +409,6 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
 // lose digits) or the sums leave the range that squares of fp32 values have
 // room in, the lane's chunk is evaluated member by member instead, with
 // eval_chunk: the results keep their precision, infinities and NaN.
-constexpr double SQRT_2LN2 = 1.17741002251547469101;  // sqrt(2 ln 2); its fp32 rounding would bias every b by 1.4e-8
-constexpr double TWO_LN2 = 1.38629436111989061883;
 constexpr int FOLD_TILE_MIN = 256;  // dims staged at once, at least (else one per lane)
 
 template <int PROB, int SM>
@@ -460,12 +458,11 @@ template <int PROB, int SM>
 __device__ __forceinline__ void fold_block(uint4 w, const float (&tr)[FoldRows<PROB, SM>::n][4], float ss, float kb,
                                            float& bl, float& even, float& small, float& odd)
 {
-    const uint32_t wr[2] = {w.x, w.z}, wa[2] = {w.y, w.w};
+    float lv[2], rv[2], cv[4];
+    bm_factors(w, lv, rv, cv);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const float l = __builtin_amdgcn_logf(__builtin_fmaf(word24(wr[h]), WORD24_SCALE, 0x1p-24f));
-        const float r = __builtin_amdgcn_sqrtf(-l), th = bm_turns(wa[h]);
-        const float cs[2] = {__builtin_amdgcn_cosf(th), __builtin_amdgcn_sinf(th)};
+        const float l = lv[h], r = rv[h], cs[2] = {cv[2 * h], cv[2 * h + 1]};
         if constexpr (FoldRows<PROB, SM>::sphere && SM == SM_SCALAR) {
             // in units of kb (even) and 2 sigma sqrt(2 ln 2) (odd)
             small += l;
@@ -988,8 +985,28 @@ __global__ __launch_bounds__(RANK_PAIRS * RANK_SLICES) void k_rank_stats(const f
 // ---------------------------------------------------------------------------
 // Weighted noise sum of one Philox block over the pairs [pb, pe):
 // a64[k] = sum_p w_p eps_{p, 4b+k}, fp32 over TELL_GROUP pairs folded into
-// fp64, in pair order.  Shared by the per-call and the fused kernels.
-template <int V>
+// fp64, in pair order.  Shared by the per-call and the fused kernels.  UNIT
+// (large runs, which no loop shares): the sums of (w_p r) cos and (w_p r) sin
+// with r in units of sqrt(2 ln 2), applied to the fp64 sums: two products a
+// pair for the weights instead of six for the normals (instructions per block
+// 59 -> 55; the kernel is bound by their number).
+template <bool UNIT>
+__device__ __forceinline__ void weigh_normals(uint4 words, float w, float a32[4])
+{
+    if constexpr (UNIT) {
+        float l[2], r[2], cs[4];
+        bm_factors(words, l, r, cs);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a32[k] = fmaf(w * r[k / 2], cs[k], a32[k]);
+    } else {
+        float e[4];
+        box_muller4(words, e);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a32[k] = fmaf(w, e[k], a32[k]);
+    }
+}
+
+template <int V, bool UNIT = false>
 __device__ __forceinline__ void tell_slice(const float* __restrict__ wr, uint32_t k0, uint32_t k1, uint32_t bb,
                                            uint32_t t, int32_t pb, int32_t pe, double a64[4])
 {
@@ -1007,12 +1024,8 @@ __device__ __forceinline__ void tell_slice(const float* __restrict__ wr, uint32_
         for (int q = 0; q < TELL_GROUP; ++q) wn[q] = wr[pn + q];
         float a32[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < TELL_GROUP; ++q) {
-            float e[4];
-            box_muller4(philox4x32_10<V>(k0, k1, bb, (uint32_t)(p0 + q), t, DOM_NOISE), e);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a32[k] = fmaf(wv[q], e[k], a32[k]);
-        }
+        for (int q = 0; q < TELL_GROUP; ++q)
+            weigh_normals<UNIT>(philox4x32_10<V>(k0, k1, bb, (uint32_t)(p0 + q), t, DOM_NOISE), wv[q], a32);
 #pragma unroll
         for (int k = 0; k < 4; ++k) a64[k] += (double)a32[k];
 #pragma unroll
@@ -1021,15 +1034,13 @@ __device__ __forceinline__ void tell_slice(const float* __restrict__ wr, uint32_
     float a32[4] = {0.f, 0.f, 0.f, 0.f};
     // the pairs past the last whole group: independent noise blocks, summed in order
 #pragma unroll 4
-    for (int32_t p = p0; p < pe; ++p) {
-        float e[4];
-        box_muller4(philox4x32_10<V>(k0, k1, bb, (uint32_t)p, t, DOM_NOISE), e);
-        const float w = wr[p];
+    for (int32_t p = p0; p < pe; ++p)
+        weigh_normals<UNIT>(philox4x32_10<V>(k0, k1, bb, (uint32_t)p, t, DOM_NOISE), wr[p], a32);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) a32[k] = fmaf(w, e[k], a32[k]);
+    for (int k = 0; k < 4; ++k) {
+        a64[k] += (double)a32[k];
+        if constexpr (UNIT) a64[k] *= SQRT_2LN2;
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) a64[k] += (double)a32[k];
 }
 
 // tell_slice with the pairs' normals of the block given (eps[p], as the
@@ -1071,6 +1082,19 @@ __device__ __forceinline__ void tell_slice_eps(const float* __restrict__ wr, con
 // b64[k] = sum_p b_p (z^2 - 1), fp32 over TELL_GROUP pairs folded into fp64.
 // ROWS: the Philox row of each item comes from rows[] (Sep-CMA-ES: the
 // elite members), else it is the item index (the pair).
+// The normals are kept in units of sqrt(2 ln 2), applied to the fp64 sums.
+__device__ __forceinline__ void weigh_squares(uint4 words, float a, float b, float a32[4], float b32[4])
+{
+    float l[2], r[2], cs[4];
+    bm_factors(words, l, r, cs);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float e = r[k / 2] * cs[k];
+        a32[k] = fmaf(a, e, a32[k]);
+        b32[k] = fmaf(b, fmaf(e, e, -(float)(1.0 / TWO_LN2)), b32[k]);
+    }
+}
+
 template <int V, bool ROWS = false>
 __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const float* __restrict__ br, uint32_t k0,
                                             uint32_t k1, uint32_t bb, uint32_t t, int32_t pb, int32_t pe,
@@ -1086,16 +1110,9 @@ __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const 
         }
         float a32[4] = {0.f, 0.f, 0.f, 0.f}, b32[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < TELL_GROUP; ++q) {
-            float e[4];
-            const uint32_t row = ROWS ? (uint32_t)rows[p0 + q] : (uint32_t)(p0 + q);
-            box_muller4(philox4x32_10<V>(k0, k1, bb, row, t, DOM_NOISE), e);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                a32[k] = fmaf(av[q], e[k], a32[k]);
-                b32[k] = fmaf(bv[q], fmaf(e[k], e[k], -1.0f), b32[k]);
-            }
-        }
+        for (int q = 0; q < TELL_GROUP; ++q)
+            weigh_squares(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p0 + q] : (uint32_t)(p0 + q), t, DOM_NOISE),
+                          av[q], bv[q], a32, b32);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             a64[k] += (double)a32[k];
@@ -1103,20 +1120,13 @@ __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const 
         }
     }
     float a32[4] = {0.f, 0.f, 0.f, 0.f}, b32[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int32_t p = p0; p < pe; ++p) {
-        float e[4];
-        box_muller4(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p] : (uint32_t)p, t, DOM_NOISE), e);
-        const float a = ar[p], b = br[p];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            a32[k] = fmaf(a, e[k], a32[k]);
-            b32[k] = fmaf(b, fmaf(e[k], e[k], -1.0f), b32[k]);
-        }
-    }
+    for (int32_t p = p0; p < pe; ++p)
+        weigh_squares(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p] : (uint32_t)p, t, DOM_NOISE), ar[p], br[p], a32,
+                      b32);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        a64[k] += (double)a32[k];
-        b64[k] += (double)b32[k];
+        a64[k] = (a64[k] + (double)a32[k]) * SQRT_2LN2;
+        b64[k] = (b64[k] + (double)b32[k]) * TWO_LN2;
     }
 }
 
@@ -1321,7 +1331,7 @@ __device__ __forceinline__ double tell_finish(const TellArgs& a, const double a6
 // pairs) and store their sums to part; k_tell_fold adds them in split order
 // and applies the update.  TWO: the second sum b (PGPE, SNES, Sep-CMA-ES);
 // ROWS: items are the elites (Sep-CMA-ES) rather than the pairs.
-template <bool TWO, bool ROWS = false, int SUB = 1, bool TEACH = false>
+template <bool TWO, bool ROWS = false, int SUB = 1, bool TEACH = false, bool UNIT = false>
 __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
 {
     if constexpr (TEACH) {
@@ -1364,7 +1374,7 @@ __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
         tell_slice2<LANES_BLOCK>(a.wfold + (int64_t)r * a.P, a.bfold + (int64_t)r * a.P, k0, k1, bb, a.t, pb, pe,
                                  a64, b64);
     else
-        tell_slice<LANES_BLOCK>(a.wfold + (int64_t)r * a.P, k0, k1, bb, a.t, pb, pe, a64);
+        tell_slice<LANES_BLOCK, UNIT>(a.wfold + (int64_t)r * a.P, k0, k1, bb, a.t, pb, pe, a64);
     // sub-slices of one block: ((l0 + l1) + (l2 + l3)) in every lane of the group
 #pragma unroll
     for (int off = 1; off < sub; off <<= 1) {
@@ -2676,11 +2686,13 @@ hipError_t launch_tell(const Geometry& g, const es_config& c, const TellPlan& tp
     if (a.tshift && !tell_carries_teacher(c, tp)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(groups + a.tshift), (unsigned)g.R, (unsigned)tp.nsplit);
     const size_t lds = sizeof(double) * (size_t)(tp.ps - 1) * TELL_LANES * (two || cma ? 8 : 4);
-    if (a.tshift) k_tell<false, false, 1, true><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
+    const bool unit = (int64_t)g.P * g.nb > EVAL_LARGE_FROM;  // no loop sums these runs (nor the MLP's)
+    if (a.tshift) k_tell<false, false, 1, true, true><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     else if (cma) k_tell<true, true><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     else if (two && sub == 4) k_tell<true, false, 4><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     else if (two) k_tell<true><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     else if (sub == 4) k_tell<false, false, 4><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
+    else if (unit) k_tell<false, false, 1, false, true><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     else k_tell<false><<<grid, TELL_LANES * tp.ps, lds, s>>>(a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
