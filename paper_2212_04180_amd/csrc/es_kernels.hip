@@ -1454,6 +1454,66 @@ __global__ __launch_bounds__(256) void k_tell_fold(TellArgs a)
     }
 }
 
+// The same fold for more than FOLD_SERIAL splits (large populations with few
+// Philox blocks).  One lane's chain of loads would set the time (65,536 members
+// with 50 dims, 1024 splits: 65 us): here a group's nbw <= 64 blocks take nbw
+// neighbouring lanes each of FOLD_MANY_WG / nbw slices, slice s sums the splits
+// s, s + slices, ..., and the slices meet in LDS pairwise, upper half onto lower
+// (8 us).
+constexpr int FOLD_SERIAL = 32;  // splits of any run that a loop sums (at most 8192 members): added in order
+constexpr int FOLD_MANY_WG = 512;
+template <bool TWO>
+__global__ __launch_bounds__(FOLD_MANY_WG) void k_tell_fold_many(TellArgs a)
+{
+    constexpr int W = TWO ? 8 : 4;
+    __shared__ double red[FOLD_MANY_WG][W];
+    const int32_t r = blockIdx.y;
+    const int64_t b0 = (int64_t)blockIdx.x * TELL_LANES;
+    const int32_t nbw = a.nb - b0 < TELL_LANES ? (int32_t)(a.nb - b0) : TELL_LANES;
+    const int32_t slices = FOLD_MANY_WG / nbw, tid = (int32_t)threadIdx.x;
+    const int32_t lb = tid % nbw, sl = tid / nbw;
+    double acc[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) acc[k] = 0.0;
+    if (sl < slices) {
+        const double* p0 = a.part + ((int64_t)r * a.nsplit * a.nb + b0 + lb) * W;
+#pragma unroll 4
+        for (int32_t z = sl; z < a.nsplit; z += slices) {
+            const double* pz = p0 + (int64_t)z * a.nb * W;
+#pragma unroll
+            for (int k = 0; k < W; ++k) acc[k] += pz[k];
+        }
+#pragma unroll
+        for (int k = 0; k < W; ++k) red[tid][k] = acc[k];
+    }
+    __syncthreads();
+    for (int32_t w = slices; w > 1;) {
+        const int32_t h = (w + 1) / 2;
+        if (sl < w - h) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) red[tid][k] += red[tid + h * nbw][k];
+        }
+        __syncthreads();
+        w = h;
+    }
+    if (tid >= TELL_LANES) return;  // the first wave finishes
+    double g2 = 0.0;
+    if (tid < nbw) {
+        double a64[4], b64[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a64[k] = red[tid][k];
+            if constexpr (TWO) b64[k] = red[tid][4 + k];
+        }
+        const uint64_t key = a.seed + (uint64_t)r;
+        g2 = tell_finish(a, a64, b64, b0 + tid, r, (uint32_t)key, (uint32_t)(key >> 32));
+    }
+    if (a.gpart) {
+        const double tot = wave_sum(g2);
+        if (tid == 0) a.gpart[(int64_t)r * gridDim.x + blockIdx.x] = tot;
+    }
+}
+
 // ClipUp (Toklu et al. 2020) after the gradient kernel, two passes over the
 // run's dims.  Each workgroup sums the per-group partials of |g|^2 (then
 // |v'|^2) in the same fixed order, so every workgroup sees the same norm.
@@ -2697,7 +2757,13 @@ hipError_t launch_tell(const Geometry& g, const es_config& c, const TellPlan& tp
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 fgrid((unsigned)((g.nb + 255) / 256), (unsigned)g.R);
-    if (tp.nsplit > 1) {
+    if (tp.nsplit > FOLD_SERIAL) {
+        const dim3 mgrid((unsigned)((g.nb + TELL_LANES - 1) / TELL_LANES), (unsigned)g.R);
+        if (two) k_tell_fold_many<true><<<mgrid, FOLD_MANY_WG, 0, s>>>(a);
+        else k_tell_fold_many<false><<<mgrid, FOLD_MANY_WG, 0, s>>>(a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else if (tp.nsplit > 1) {
         if (two) k_tell_fold<true><<<fgrid, 256, 0, s>>>(a);
         else k_tell_fold<false><<<fgrid, 256, 0, s>>>(a);
         e = hipGetLastError();
