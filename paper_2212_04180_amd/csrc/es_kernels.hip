@@ -1105,19 +1105,6 @@ __device__ __forceinline__ void tell_slice_eps(const float* __restrict__ wr, con
 // b64[k] = sum_p b_p (z^2 - 1), fp32 over TELL_GROUP pairs folded into fp64.
 // ROWS: the Philox row of each item comes from rows[] (Sep-CMA-ES: the
 // elite members), else it is the item index (the pair).
-// The normals are kept in units of sqrt(2 ln 2), applied to the fp64 sums.
-__device__ __forceinline__ void weigh_squares(uint4 words, float a, float b, float a32[4], float b32[4])
-{
-    float l[2], r[2], cs[4];
-    bm_factors(words, l, r, cs);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float e = r[k / 2] * cs[k];
-        a32[k] = fmaf(a, e, a32[k]);
-        b32[k] = fmaf(b, fmaf(e, e, -(float)(1.0 / TWO_LN2)), b32[k]);
-    }
-}
-
 template <int V, bool ROWS = false>
 __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const float* __restrict__ br, uint32_t k0,
                                             uint32_t k1, uint32_t bb, uint32_t t, int32_t pb, int32_t pe,
@@ -1133,9 +1120,16 @@ __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const 
         }
         float a32[4] = {0.f, 0.f, 0.f, 0.f}, b32[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < TELL_GROUP; ++q)
-            weigh_squares(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p0 + q] : (uint32_t)(p0 + q), t, DOM_NOISE),
-                          av[q], bv[q], a32, b32);
+        for (int q = 0; q < TELL_GROUP; ++q) {
+            float e[4];
+            const uint32_t row = ROWS ? (uint32_t)rows[p0 + q] : (uint32_t)(p0 + q);
+            box_muller4(philox4x32_10<V>(k0, k1, bb, row, t, DOM_NOISE), e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                a32[k] = fmaf(av[q], e[k], a32[k]);
+                b32[k] = fmaf(bv[q], fmaf(e[k], e[k], -1.0f), b32[k]);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             a64[k] += (double)a32[k];
@@ -1143,13 +1137,20 @@ __device__ __forceinline__ void tell_slice2(const float* __restrict__ ar, const 
         }
     }
     float a32[4] = {0.f, 0.f, 0.f, 0.f}, b32[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int32_t p = p0; p < pe; ++p)
-        weigh_squares(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p] : (uint32_t)p, t, DOM_NOISE), ar[p], br[p], a32,
-                      b32);
+    for (int32_t p = p0; p < pe; ++p) {
+        float e[4];
+        box_muller4(philox4x32_10<V>(k0, k1, bb, ROWS ? (uint32_t)rows[p] : (uint32_t)p, t, DOM_NOISE), e);
+        const float a = ar[p], b = br[p];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a32[k] = fmaf(a, e[k], a32[k]);
+            b32[k] = fmaf(b, fmaf(e[k], e[k], -1.0f), b32[k]);
+        }
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        a64[k] = (a64[k] + (double)a32[k]) * SQRT_2LN2;
-        b64[k] = (b64[k] + (double)b32[k]) * TWO_LN2;
+        a64[k] += (double)a32[k];
+        b64[k] += (double)b32[k];
     }
 }
 
