@@ -12,6 +12,8 @@
 #include <cstdlib>
 #include <algorithm>
 #include <cstring>
+#include <initializer_list>
+#include <utility>
 #include <vector>
 #include <new>
 
@@ -388,12 +390,48 @@ hipError_t copy_rows(const Geometry& g, float* dst, size_t dpitch, const float* 
     return hipSuccess;
 }
 
-es_status copy_rows_out(es_handle* h, float* dst, const float* src)
+// Whether a kernel of this handle can store to p as a copy command would:
+// device memory of the handle's own device, 4-byte aligned.
+bool kernel_can_store(const es_handle* h, const void* p)
 {
-    const Geometry& g = h->g;
-    ES_HIP(h, copy_rows(g, dst, (size_t)g.D * 4, src, (size_t)g.Dp * 4, h->stream), "copy out");
+    if (reinterpret_cast<uintptr_t>(p) & 3) return false;
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == h->device;
+}
+
+// Several state arrays out (entries with a null dst are skipped): one launch
+// for all of them, or a copy command each where a destination is not plain
+// memory of the handle's device.
+es_status copy_out(es_handle* h, int64_t rows, int64_t D, std::initializer_list<std::pair<float*, const float*>> arrays)
+{
+    float* dst[EXPORT_MAX];
+    const float* src[EXPORT_MAX];
+    int n = 0;
+    bool kernel = true;
+    for (const auto& a : arrays) {
+        if (!a.first) continue;
+        dst[n] = a.first;
+        src[n++] = a.second;
+        kernel = kernel && kernel_can_store(h, a.first);
+    }
+    if (n > 1 && kernel) {
+        ES_HIP(h, launch_export_rows(rows, D, n, dst, src, h->stream), "copy out");
+        return ES_OK;
+    }
+    Geometry g{};
+    g.R = (int32_t)rows;
+    g.D = D;
+    g.Dp = (D + 3) / 4 * 4;
+    for (int k = 0; k < n; ++k)
+        ES_HIP(h, copy_rows(g, dst[k], (size_t)D * 4, src[k], (size_t)g.Dp * 4, h->stream), "copy out");
     return ES_OK;
 }
+
+es_status copy_rows_out(es_handle* h, float* dst, const float* src) { return copy_out(h, h->g.R, h->g.D, {{dst, src}}); }
 
 es_status copy_rows_in(es_handle* h, float* dst, const float* src)
 {
@@ -733,10 +771,8 @@ es_status es_run(es_handle* h, int32_t T, float* log)
 es_status es_get_state(es_handle* h, float* m, float* m1, float* v, int64_t* t)
 {
     if (!h) return ES_ERR_ARG;
-    es_status s = ES_OK;
-    if (m && (s = copy_rows_out(h, m, h->m)) != ES_OK) return s;
-    if (m1 && (s = copy_rows_out(h, m1, h->m1)) != ES_OK) return s;
-    if (v && (s = copy_rows_out(h, v, h->v)) != ES_OK) return s;
+    const es_status s = copy_out(h, h->g.R, h->g.D, {{m, h->m}, {m1, h->m1}, {v, h->v}});
+    if (s != ES_OK) return s;
     if (t) *t = h->t;
     return ES_OK;
 }
@@ -784,10 +820,9 @@ es_status es_get_best(es_handle* h, float* member, float* fitness)
 es_status es_get_shaped(es_handle* h, float* y, int32_t* rank)
 {
     if (!h) return ES_ERR_ARG;
-    const size_t n = (size_t)h->g.N * h->g.R;
-    if (y) ES_HIP(h, hipMemcpyAsync(y, h->y, n * 4, hipMemcpyDeviceToDevice, h->stream), "copy y");
-    if (rank) ES_HIP(h, hipMemcpyAsync(rank, h->rank, n * 4, hipMemcpyDeviceToDevice, h->stream), "copy ranks");
-    return ES_OK;
+    // dense [R N] arrays of 4-byte words
+    return copy_out(h, 1, (int64_t)h->g.N * h->g.R,
+                    {{y, h->y}, {reinterpret_cast<float*>(rank), reinterpret_cast<const float*>(h->rank)}});
 }
 
 es_status es_get_grad(es_handle* h, float* g)
@@ -836,11 +871,8 @@ es_status es_get_strategy_state(es_handle* h, float* sigma_vec, float* velocity)
     if (!h) return ES_ERR_ARG;
     if ((sigma_vec && !h->sig) || (velocity && !h->vel))
         return fail(h, ES_ERR_UNSUPPORTED, "es_get_strategy_state: the strategy keeps no such state");
-    es_status s = ES_OK;
     // Sep-CMA-ES: the diagonal covariance (its sampling scale is derived)
-    if (sigma_vec && (s = copy_rows_out(h, sigma_vec, h->cmaC ? h->cmaC : h->sig)) != ES_OK) return s;
-    if (velocity && (s = copy_rows_out(h, velocity, h->vel)) != ES_OK) return s;
-    return ES_OK;
+    return copy_out(h, h->g.R, h->g.D, {{sigma_vec, h->cmaC ? h->cmaC : h->sig}, {velocity, h->vel}});
 }
 
 es_status es_set_strategy_state(es_handle* h, const float* sigma_vec, const float* velocity)

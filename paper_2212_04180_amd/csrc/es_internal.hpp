@@ -58,6 +58,15 @@ hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m
                        float* best_x, hipStream_t s);
 hipError_t launch_problem_data(const Geometry& g, const es_config& c, float* pdata, hipStream_t s);
 hipError_t launch_fill_rows(const Geometry& g, float* p, float value, hipStream_t s);  // [R][Dp], padding 0
+// State rows (row stride 4 ceil(D / 4), 16-byte aligned) into dense [rows][D]
+// arrays (4-byte aligned device memory), n <= EXPORT_MAX at once.
+constexpr int EXPORT_MAX = 4;
+struct ExportArgs {
+    float* dst[EXPORT_MAX];
+    const float* src[EXPORT_MAX];
+    int64_t rows, D, nb, total;
+};
+hipError_t launch_export_rows(int64_t rows, int64_t D, int n, float* const* dst, const float* const* src, hipStream_t s);
 hipError_t launch_cma_scale(const Geometry& g, float* svec, const float* C, const float* hp, hipStream_t s);
 // hp: device [2][R], sigma then lr of every run for the current generation.
 // svec: per-dimension sigma [R][Dp] (PGPE, SNES) or null.

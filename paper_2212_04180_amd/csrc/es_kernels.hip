@@ -2525,6 +2525,36 @@ __global__ void k_fill_rows(float* __restrict__ p, float value, int64_t D, int64
         p[i] = (i % Dp) < D ? value : 0.0f;
 }
 
+// Up to EXPORT_MAX arrays out of the state's padded rows [R][4 nb] into dense
+// [R][D] ones, one launch for all of them (blockIdx.y): a copy command per
+// array costs a launch of its own, 2-5 us each at a few MB.  Lane = four dims;
+// a dense row starts on a 4-byte boundary.
+__global__ __launch_bounds__(256) void k_export_rows(ExportArgs a)
+{
+    const float* __restrict__ src = a.src[blockIdx.y];
+    float* __restrict__ dst = a.dst[blockIdx.y];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.total; i += (int64_t)gridDim.x * 256) {
+        const float4 v = *reinterpret_cast<const float4*>(src + 4 * i);
+        int64_t b = i, o = 4 * i;
+        if (a.rows > 1) {
+            const int64_t r = a.total >> 32 ? i / a.nb : (int64_t)((uint32_t)i / (uint32_t)a.nb);
+            b = i - r * a.nb;
+            o = r * a.D + 4 * b;
+        }
+        const float e[4] = {v.x, v.y, v.z, v.w};
+        if (4 * b + 4 <= a.D) {
+            float4u u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = e[k];
+            *reinterpret_cast<float4u*>(dst + o) = u;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (4 * b + k < a.D) dst[o + k] = e[k];
+        }
+    }
+}
+
 int grid_for(int64_t n, int threads)
 {
     const int64_t g = (n + threads - 1) / threads;
@@ -2630,6 +2660,22 @@ hipError_t launch_fill_rows(const Geometry& g, float* p, float value, hipStream_
 {
     const int64_t total = g.Dp * (int64_t)g.R;
     k_fill_rows<<<grid_for(total, 256), 256, 0, s>>>(p, value, g.D, g.Dp, total);
+    return hipGetLastError();
+}
+
+hipError_t launch_export_rows(int64_t rows, int64_t D, int n, float* const* dst, const float* const* src, hipStream_t s)
+{
+    ExportArgs a{};
+    const bool dense = rows == 1 || D % 4 == 0;  // no padding between the rows
+    a.rows = dense ? 1 : rows;
+    a.D = dense ? rows * D : D;
+    a.nb = (a.D + 3) / 4;
+    a.total = a.rows * a.nb;
+    for (int k = 0; k < n; ++k) {
+        a.dst[k] = dst[k];
+        a.src[k] = src[k];
+    }
+    k_export_rows<<<dim3((unsigned)grid_for(a.total, 256), (unsigned)n), 256, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,34 @@
+"""State read out by one launch (marked gpu): every array of a ragged, several-run
+state equals the one read by itself, and nothing beyond the dense rows is written."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,R", [(1, 1), (1, 5), (3, 2), (4, 3), (7, 300), (1023, 4), (1026, 1), (70001, 3)])
+def test_state_and_strategy_state_out(D, R):
+    import paper_2212_04180_amd as P
+    es = P.ES(P.ESConfig(num_dims=D, popsize=6, num_runs=R, seed=3, problem=P.PROB_SPHERE, strategy=P.STRAT_PGPE,
+                         optimizer=P.OPT_CLIPUP))
+    rng = np.random.default_rng(D)
+    src = [torch.from_numpy(rng.normal(size=(R, D)).astype(np.float32)).cuda() for _ in range(5)]
+    es.set_state(src[0], src[1], src[2], 7)
+    es.set_strategy_state(src[3].abs(), src[4])
+    L, h = P.lib(), es._h
+    t = ctypes.c_int64()
+    buf = torch.full((3, R * D + 8), -9.0, device="cuda")  # rows at 4-byte offsets 1, 2, 3
+    at = [buf[k][1 + k:1 + k + R * D] for k in range(3)]
+    es._check(L.es_get_state(h, *[ctypes.c_void_p(a.data_ptr()) for a in at], ctypes.byref(t)))
+    got = buf.cpu().numpy()
+    for k in range(3):
+        np.testing.assert_array_equal(got[k, 1 + k:1 + k + R * D], src[k].cpu().numpy().ravel())
+        assert np.all(got[k, :1 + k] == -9.0) and np.all(got[k, 1 + k + R * D:] == -9.0)
+    alone = torch.empty(R, D, device="cuda")
+    es._check(L.es_get_state(h, None, ctypes.c_void_p(alone.data_ptr()), None, ctypes.byref(t)))
+    assert torch.equal(alone, src[1]) and t.value == 7
+    sg, ve = es.strategy_state(velocity=True)
+    assert torch.equal(sg, src[3].abs()) and torch.equal(ve, src[4])
