@@ -495,7 +495,7 @@ es_status es_init(const es_config* cfg, void* hip_stream, es_handle** out)
     g.N = cfg->popsize;
     g.P = cfg->popsize / 2;
     g.R = cfg->num_runs;
-    h->plan = eval_plan(g, cfg->plan_eval_blocks);
+    h->plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy == ES_STRAT_SEP_CMA);
     // where es_run takes the fused loop (the rule of es_run), the per-call
     // gradient kernel sums in the fused loop's order, so both give the same bits
     h->tell = tell_plan(g, fused_by_default(g, h->plan, *cfg), cfg->plan_tell_split);
@@ -687,7 +687,7 @@ es_status es_eval_noalloc(const es_config* cfg, const float* mean, const float* 
     g.N = cfg->popsize;
     g.P = cfg->popsize / 2;
     g.R = cfg->num_runs;
-    const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks);
+    const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks, false);
     const int64_t need = eval_partial_elems(g, plan);
     if (need > (int64_t)NOALLOC_SCRATCH_FLOATS) {
         std::snprintf(g_init_err, sizeof(g_init_err),

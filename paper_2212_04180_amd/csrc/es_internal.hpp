@@ -44,6 +44,7 @@ struct EvalPlan {
     int32_t n_pg;     // pair groups per run
     int64_t bc;       // blocks per chunk
     int64_t nchunks;  // chunks per member
+    bool small;       // one launch (k_eval_small) instead of evaluate and reduction
     bool folded;      // even and odd sums of a pair (k_eval_fold) instead of its two members
 };
 // Runs of more pair-blocks (P nb) than this have an evaluate plan of their own:
@@ -51,7 +52,8 @@ struct EvalPlan {
 // stored normals' blocks in 16 x 144 KB), so their sums need not follow the
 // loops' order.
 constexpr int64_t EVAL_LARGE_FROM = 1 << 18;
-EvalPlan eval_plan(const Geometry& g, int64_t bc_override);
+// indep: independent members (Sep-CMA-ES) instead of antithetic pairs
+EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep);
 int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e);  // floats
 
 hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m1, float* v,

@@ -32,6 +32,7 @@
 #include <math.h>
 #include <stddef.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -667,6 +668,63 @@ __global__ __launch_bounds__(64 * RED_SLICES) void k_eval_reduce(const float* __
 #pragma unroll
         for (int q = 0; q < RED_SLICES; ++q) tot += red[q][tx];
         fit[(int64_t)r * N + j] = (float)(tot / div);
+    }
+}
+
+// Evaluate and reduction in one launch: a workgroup takes every chunk of pw
+// pairs, one (pair, chunk) item per lane, and sums the chunks' partials from LDS
+// in the reduce kernel's order (so the same bits).  pw as small as one pass over
+// the items allows, so that the workgroups spread over the CUs.  Small evaluates
+// are bound by the chain of launch, Philox rounds and exchanges, which this
+// halves (1000 dims x 256 members: 5.8 -> 3.7 us), larger ones by VALU issue
+// (both counter words vary across the lanes: 39 Philox instructions instead of
+// 33); the plan says where the line lies.
+constexpr int SMALL_WG = 256;
+constexpr int SMALL_MAX_CHUNKS = 4 * SMALL_WG;
+constexpr int SMALL_MAX_PAIRS = 64;  // pairs per workgroup: 16 KB of slice sums, and every member a lane
+template <int PROB, int SM>
+__global__ __launch_bounds__(SMALL_WG) void k_eval_small(const float* __restrict__ m, const float* __restrict__ pdata,
+                                                         float* __restrict__ fit, uint64_t seed, uint32_t t, int64_t D,
+                                                         int64_t nb, int32_t N, int32_t P, int64_t bc, int32_t nchunks,
+                                                         int32_t pw, const float* __restrict__ hp, float ra,
+                                                         const float* __restrict__ svec, double add, double div)
+{
+    extern __shared__ __align__(16) double smem[];
+    double* slice = smem;                                             // [RED_SLICES][2 pw]
+    float* part = reinterpret_cast<float*>(slice + RED_SLICES * 2 * pw);  // [nchunks][2 pw]
+    const int32_t r = blockIdx.y, p0 = (int32_t)blockIdx.x * pw, w2 = 2 * pw;
+    const float sigma = hp[r];
+    const uint64_t key = seed + (uint64_t)r;
+    const float* __restrict__ mr = m + (int64_t)r * 4 * nb;
+    const float* __restrict__ gr = SM != SM_SCALAR ? svec + (int64_t)r * 4 * nb : nullptr;
+    const int32_t i = (int32_t)threadIdx.x;
+    static_assert(2 * SMALL_MAX_PAIRS <= SMALL_WG, "the last phase gives every member a lane");
+    for (int32_t k = i; k < pw * nchunks; k += SMALL_WG) {  // one pass where pw > 1
+        const int32_t pl = k % pw, c = k / pw;
+        const int32_t p = p0 + pl < P ? p0 + pl : P - 1;
+        const int64_t b0 = (int64_t)c * bc, b1 = b0 + bc < nb ? b0 + bc : nb;
+        double accp, accm;
+        eval_chunk<PROB, LANES_BLOCK_AND_ROW, SM>(mr, pdata, (uint32_t)key, (uint32_t)(key >> 32), (uint32_t)p, t, b0, b1,
+                                                  D, sigma, ra, accp, accm, gr, (uint32_t)(p + P));
+        part[c * w2 + pl] = (float)accp;
+        part[c * w2 + pw + pl] = (float)accm;
+    }
+    __syncthreads();
+    for (int32_t k = i; k < RED_SLICES * w2; k += SMALL_WG) {
+        const int32_t q = k / w2, j = k - q * w2;
+        double acc = 0.0;
+        for (int32_t cc = q; cc < nchunks; cc += RED_SLICES) acc += (double)part[cc * w2 + j];
+        slice[k] = acc;
+    }
+    __syncthreads();
+    if (i < w2 && p0 + i % pw < P) {
+        double v[RED_SLICES];
+#pragma unroll
+        for (int q = 0; q < RED_SLICES; ++q) v[q] = slice[q * w2 + i];
+        double tot = add;
+#pragma unroll
+        for (int q = 0; q < RED_SLICES; ++q) tot += v[q];
+        fit[(int64_t)r * N + p0 + i % pw + (i < pw ? 0 : P)] = (float)(tot / div);
     }
 }
 
@@ -2596,7 +2654,7 @@ static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e)
     return best;
 }
 
-EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
+EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
 {
     EvalPlan e;
     const int32_t P64 = (g.P + 63) / 64 * 64;
@@ -2604,12 +2662,29 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
     e.n_pg = (g.P + e.wg - 1) / e.wg;
     const int64_t waves_per_chunk = (int64_t)e.n_pg * (e.wg / 64) * g.R;
     const bool large = (int64_t)g.P * g.nb > EVAL_LARGE_FROM;
+    const double pair_blocks = (double)g.R * g.P * g.nb, wave_blocks = (double)waves_per_chunk * g.nb;
+    // One launch for evaluate and reduction while the second launch, its chain
+    // of loads and the chunks' start-ups cost more than a workgroup of one or a
+    // few pairs does: for a run of its own plan up to 6e6 pair-blocks, more
+    // where the other kernels leave lanes idle (fewer than 64 pairs, squared by
+    // the share), with at least 96 workgroups.  Evaluate in us, two launches /
+    // one (sphere, Rastrigin): 1000 dims x 256 members 5.8 / 3.7, 6.0 / 4.2;
+    // 100 x 64 x 1024 runs 10.6 / 5.3, 12.5 / 6.3; 20,000 x 256 9.3 / 6.9, 11.1 /
+    // 8.2; 10,007 x 1024 x 2 12.3 / 9.4, 14.8 / 11.9; 50,001 x 510 15.1 / 12.3,
+    // 18.7 / 16.0; 40,528 x 1096 (5.6e6) 22.2 / 20.2, 28.4 / 28.1; 20,000 x 1000 x 4
+    // (1.0e7) 27.0 / 24.9, 34.5 / 34.8; 100,001 x 510 x 2 (1.3e7) 32.2 / 31.8, 42.1 /
+    // 45.2; with half the lanes idle 200,000 x 64 x 8 (1.3e7) 52.6 / 47.3, 72.7 /
+    // 61.0; 60,000 x 64 (32 workgroups) 11.9 / 13.3, 13.1 / 18.0.  Independent
+    // members take twice the noise and registers: one launch only for the runs
+    // of the smaller plan (10,007 x 1024 x 2 20.0 / 23.2, 50,001 x 510 25.9 / 32.3).
+    const double spread = wave_blocks * 64.0 / pair_blocks;
+    e.small = !large || (!indep && pair_blocks <= 6e6 * spread * spread && (int64_t)g.R * g.P >= 96);
     // Even and odd sums save VALU instructions and cost a staged tile per
     // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, members /
     // folded at their best chunks, shifted sphere: 36,000 12.7 / 14.1; 40,032
     // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
     // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
-    e.folded = large && g.P >= 2 && waves_per_chunk * g.nb >= (1 << 16);
+    e.folded = !e.small && !indep && large && g.P >= 2 && wave_blocks >= 65536.0;
     int64_t bc;
     if (bc_override > 0) {
         bc = bc_override;
@@ -2623,7 +2698,7 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
         if (nch < 1) nch = 1;
         bc = (g.nb + nch - 1) / nch;
         if (bc < EVAL_FOLD) bc = EVAL_FOLD;
-        if (large) bc = eval_chunk_blocks(g, e);
+        if (large) bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e);
         // a small run: chunks short enough that the fused loop's workgroup
         // takes every (pair, chunk) item at once
         if ((int64_t)g.P * g.nb <= (int64_t)FUSED_WG * EVAL_FOLD) {
@@ -2635,6 +2710,7 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override)
     if (bc > g.nb) bc = g.nb;
     e.bc = bc;
     e.nchunks = (g.nb + bc - 1) / bc;
+    e.small = e.small && e.nchunks <= SMALL_MAX_CHUNKS;  // its partials in LDS, at most four passes over the chunks
     return e;
 }
 
@@ -2711,6 +2787,27 @@ hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPla
                             const float* hp, const float* svec, double div, hipStream_t s, hipEvent_t ev_start,
                             hipEvent_t ev_stop)
 {
+    const double add = c.problem == ES_PROB_RASTRIGIN ? (double)c.rastrigin_a * (double)g.D : 0.0;
+    if (e.small) {
+        const int sm = c.strategy == ES_STRAT_SEP_CMA ? SM_INDEP : svec ? SM_VEC : SM_SCALAR;
+        const int32_t pw = std::max(1, std::min(std::min(SMALL_WG / (int32_t)e.nchunks, SMALL_MAX_PAIRS), g.P));
+        const dim3 sgrid((unsigned)((g.P + pw - 1) / pw), (unsigned)g.R);
+        const uint32_t lds = (uint32_t)(2 * pw * (sizeof(double) * RED_SLICES + sizeof(float) * e.nchunks));
+#define ES_SMALL(PROB, SM)                                                                                             \
+    launch_timed(k_eval_small<PROB, SM>, sgrid, dim3(SMALL_WG), lds, s, ev_start, ev_stop, m, pdata, fit, c.seed, t, g.D, \
+                 g.nb, g.N, g.P, e.bc, (int32_t)e.nchunks, pw, hp, c.rastrigin_a, svec, add, div)
+#define ES_SMALL_PROB(PROB) \
+    (sm == SM_INDEP ? ES_SMALL(PROB, SM_INDEP) : sm == SM_VEC ? ES_SMALL(PROB, SM_VEC) : ES_SMALL(PROB, SM_SCALAR))
+        switch (c.problem) {
+        case ES_PROB_SPHERE: return ES_SMALL_PROB(ES_PROB_SPHERE);
+        case ES_PROB_SHIFTED_SPHERE: return ES_SMALL_PROB(ES_PROB_SHIFTED_SPHERE);
+        case ES_PROB_ROSENBROCK: return ES_SMALL_PROB(ES_PROB_ROSENBROCK);
+        case ES_PROB_RASTRIGIN: return ES_SMALL_PROB(ES_PROB_RASTRIGIN);
+        default: return hipErrorInvalidValue;
+        }
+#undef ES_SMALL_PROB
+#undef ES_SMALL
+    }
     // chunk ids are dealt so that the pair groups of one chunk share an XCD
     const int64_t slots = (e.nchunks + 7) / 8 * e.n_pg;
     const dim3 grid((unsigned)(slots * 8), (unsigned)g.R);
@@ -2741,7 +2838,6 @@ hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPla
 #undef ES_EVAL_LAUNCH
 #undef ES_EVAL_ARGS
     if (err != hipSuccess) return err;
-    const double add = c.problem == ES_PROB_RASTRIGIN ? (double)c.rastrigin_a * (double)g.D : 0.0;
     return launch_timed(k_eval_reduce, dim3((unsigned)((g.N + 63) / 64), (unsigned)g.R), dim3(64 * RED_SLICES), 0, s,
                         nullptr, nullptr, (const float*)partial, fit, g.N, g.R, e.nchunks, add, div);
 }
