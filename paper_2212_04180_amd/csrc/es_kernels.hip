@@ -1284,6 +1284,28 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// What an update reads of its block's state.  Kernels whose few workgroups wait
+// on these loads issue them ahead of their sums; the large gradient kernel reads
+// them after (eight waves per SIMD hide them, and the registers would cost one).
+struct TellRows {
+    float4 m4, s4, m14, v4;
+    float sigma, lr;
+    int32_t jb;
+};
+__device__ __forceinline__ TellRows tell_rows(const TellArgs& a, int64_t b, int32_t r)
+{
+    TellRows t;
+    const int64_t off = (int64_t)r * 4 * a.nb + 4 * b;
+    t.sigma = a.hp[r];
+    t.lr = a.hp[a.R + r];
+    t.jb = a.best_j[r];
+    t.m4 = *reinterpret_cast<const float4*>(a.m + off);
+    t.m14 = *reinterpret_cast<const float4*>(a.m1 + off);
+    t.v4 = *reinterpret_cast<const float4*>(a.v + off);
+    t.s4 = a.sig ? *reinterpret_cast<const float4*>(a.sig + off) : make_float4(t.sigma, t.sigma, t.sigma, t.sigma);
+    return t;
+}
+
 // Update of one Philox block from its noise sums a64 (and b64):
 //   OpenAI-ES  g = a / (N sigma), Adam (or ClipUp, stepped later);
 //   PGPE       g = sigma_d a / N, Adam or ClipUp on the mean;
@@ -1292,26 +1314,20 @@ __device__ __forceinline__ double wave_sum(double v)
 // Also the best member's parameters when the generation improved on the
 // best so far (old mean and sigma), and the gradient when asked for.
 // Returns this lane's share of |g|^2 (ClipUp), else 0.
-__device__ __forceinline__ double tell_finish(const TellArgs& a, const double a64[4], const double b64[4], int64_t b,
-                                              int32_t r, uint32_t k0, uint32_t k1)
+__device__ __forceinline__ double tell_finish(const TellArgs& a, const TellRows& t, const double a64[4],
+                                              const double b64[4], int64_t b, int32_t r, uint32_t k0, uint32_t k1)
 {
     const int64_t off = (int64_t)r * 4 * a.nb + 4 * b;
-    const float sigma = a.hp[r], lr = a.hp[a.R + r];
-    const float4 m4 = *reinterpret_cast<const float4*>(a.m + off);
-    const float mo[4] = {m4.x, m4.y, m4.z, m4.w};
-    float so[4] = {sigma, sigma, sigma, sigma};
-    if (a.sig) {
-        const float4 s4 = *reinterpret_cast<const float4*>(a.sig + off);
-        so[0] = s4.x; so[1] = s4.y; so[2] = s4.z; so[3] = s4.w;
-    }
+    const float sigma = t.sigma, lr = t.lr;
+    const float mo[4] = {t.m4.x, t.m4.y, t.m4.z, t.m4.w};
+    const float so[4] = {t.s4.x, t.s4.y, t.s4.z, t.s4.w};
     const int32_t N = 2 * a.P;
     float mn[4] = {mo[0], mo[1], mo[2], mo[3]}, gg[4] = {0.f, 0.f, 0.f, 0.f}, sn[4] = {so[0], so[1], so[2], so[3]};
     double g2 = 0.0;
     if (a.strategy == ES_STRAT_SEP_CMA) {
         // first pass: mean, p_sigma (in m1), the sums for the second pass and
         // this lane's share of |p_sigma|^2; the best member (row = member, + sign)
-        const float4 p4 = *reinterpret_cast<const float4*>(a.m1 + off);
-        const float po[4] = {p4.x, p4.y, p4.z, p4.w};
+        const float po[4] = {t.m14.x, t.m14.y, t.m14.z, t.m14.w};
         float pn[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1324,7 +1340,7 @@ __device__ __forceinline__ double tell_finish(const TellArgs& a, const double a6
         *reinterpret_cast<double4*>(a.qd + off) =
             make_double4(b64[0] + a.cma.wsum, b64[1] + a.cma.wsum, b64[2] + a.cma.wsum, b64[3] + a.cma.wsum);
         *reinterpret_cast<float4*>(a.m1 + off) = make_float4(pn[0], pn[1], pn[2], pn[3]);
-        const int32_t jb = a.best_j[r];
+        const int32_t jb = t.jb;
         if (jb >= 0) {
             float e[4];
             box_muller4(philox4x32_10<LANES_BLOCK>(k0, k1, (uint32_t)b, (uint32_t)jb, a.t, DOM_NOISE), e);
@@ -1364,10 +1380,8 @@ __device__ __forceinline__ double tell_finish(const TellArgs& a, const double a6
 #pragma unroll
             for (int k = 0; k < 4; ++k) g2 += (double)gg[k] * (double)gg[k];
         } else {
-            const float4 m14 = *reinterpret_cast<const float4*>(a.m1 + off);
-            const float4 v4 = *reinterpret_cast<const float4*>(a.v + off);
-            const float m1o[4] = {m14.x, m14.y, m14.z, m14.w};
-            const float vo[4] = {v4.x, v4.y, v4.z, v4.w};
+            const float m1o[4] = {t.m14.x, t.m14.y, t.m14.z, t.m14.w};
+            const float vo[4] = {t.v4.x, t.v4.y, t.v4.z, t.v4.w};
             float m1n[4], vn[4], gd[4];
             const double a1[4] = {(double)gg[0], (double)gg[1], (double)gg[2], (double)gg[3]};
             adam_block(a1, 1.0, a.ac, lr, 4 * b, a.D, mo, m1o, vo, mn, m1n, vn, gd);
@@ -1386,7 +1400,7 @@ __device__ __forceinline__ double tell_finish(const TellArgs& a, const double a6
             }
         }
     }
-    const int32_t jb = a.best_j[r];
+    const int32_t jb = t.jb;
     if (jb >= 0) {
         const int32_t pbst = jb < a.P ? jb : jb - a.P;
         float e[4];
@@ -1450,6 +1464,8 @@ __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
     const int32_t pe = (int32_t)(((int64_t)a.nitems * (gs + 1)) / S);
 
     double a64[4] = {0.0, 0.0, 0.0, 0.0}, b64[4] = {0.0, 0.0, 0.0, 0.0};
+    TellRows rows{};
+    if (SUB > 1 && s == 0) rows = tell_rows(a, (int64_t)bb, r);
     if constexpr (ROWS)
         tell_slice2<LANES_BLOCK, true>(a.cw, a.cw, k0, k1, bb, a.t, pb, pe, a64, b64, a.elite + (int64_t)r * 2 * a.P);
     else if constexpr (TWO)
@@ -1490,7 +1506,8 @@ __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
         return;
     }
     if (SUB > 1 && si != 0) return;  // SUB > 1 only where no per-wave norm partials are kept
-    const double g2 = b < a.nb ? tell_finish(a, a64, b64, b, r, k0, k1) : 0.0;
+    if (SUB == 1 && b < a.nb) rows = tell_rows(a, b, r);
+    const double g2 = b < a.nb ? tell_finish(a, rows, a64, b64, b, r, k0, k1) : 0.0;
     if (a.gpart) {
         const double tot = wave_sum(g2);
         if (tx == 0) a.gpart[(int64_t)r * gn + gx] = tot;
@@ -1510,6 +1527,7 @@ __global__ __launch_bounds__(256) void k_tell_fold(TellArgs a)
     double g2 = 0.0;
     if (b < a.nb) {
         constexpr int W = TWO ? 8 : 4;
+        const TellRows rows = tell_rows(a, b, r);
         const double* p0 = a.part + ((int64_t)r * a.nsplit * a.nb + b) * W;
         double a64[4], b64[4] = {0.0, 0.0, 0.0, 0.0};
         const double4 q0 = *reinterpret_cast<const double4*>(p0);
@@ -1527,7 +1545,7 @@ __global__ __launch_bounds__(256) void k_tell_fold(TellArgs a)
                 b64[0] += rr.x; b64[1] += rr.y; b64[2] += rr.z; b64[3] += rr.w;
             }
         }
-        g2 = tell_finish(a, a64, b64, b, r, k0, k1);
+        g2 = tell_finish(a, rows, a64, b64, b, r, k0, k1);
     }
     if (a.gpart) {
         const double tot = wave_sum(g2);
@@ -1557,6 +1575,8 @@ __global__ __launch_bounds__(FOLD_MANY_WG) void k_tell_fold_many(TellArgs a)
     double acc[W];
 #pragma unroll
     for (int k = 0; k < W; ++k) acc[k] = 0.0;
+    TellRows rows{};
+    if (tid < nbw) rows = tell_rows(a, b0 + tid, r);
     if (sl < slices) {
         const double* p0 = a.part + ((int64_t)r * a.nsplit * a.nb + b0 + lb) * W;
 #pragma unroll 4
@@ -1588,7 +1608,7 @@ __global__ __launch_bounds__(FOLD_MANY_WG) void k_tell_fold_many(TellArgs a)
             if constexpr (TWO) b64[k] = red[tid][4 + k];
         }
         const uint64_t key = a.seed + (uint64_t)r;
-        g2 = tell_finish(a, a64, b64, b0 + tid, r, (uint32_t)key, (uint32_t)(key >> 32));
+        g2 = tell_finish(a, rows, a64, b64, b0 + tid, r, (uint32_t)key, (uint32_t)(key >> 32));
     }
     if (a.gpart) {
         const double tot = wave_sum(g2);
