@@ -44,6 +44,7 @@ struct EvalPlan {
     int32_t n_pg;     // pair groups per run
     int64_t bc;       // blocks per chunk
     int64_t nchunks;  // chunks per member
+    int64_t partial_chunks;  // chunks that a partials buffer has room for
     bool small;       // one launch (k_eval_small) instead of evaluate and reduction
     bool folded;      // even and odd sums of a pair (k_eval_fold) instead of its two members
 };

@@ -2652,14 +2652,21 @@ int grid_for(int64_t n, int threads)
 // members 46 / 24, 200,000 x 64 57 / 20, 50,001 x 510 30 / 16, 100,001 x 510 x 2
 // runs 40 / 35, 250,003 x 1000 73 / 66, 3000 x 2048 x 3 15.3 / 12.7, 1e6 x 2048
 // 411 / 411.
-static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e)
+//
+// The partials stay within the smaller runs' plan's (ref_chunks) or the static
+// scratch, whichever is larger: the estimate alone would take gigabytes for
+// many runs or dimensions (94 runs of 12,788 members in 1.7e6 dims: 8.7 GB).
+static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e, int64_t ref_chunks)
 {
+    const int64_t members = g.R * (int64_t)g.N;
+    const int64_t most = std::max<int64_t>(ref_chunks, (int64_t)NOALLOC_SCRATCH_FLOATS / members);
     const int64_t per_chunk = (int64_t)e.n_pg * g.R;  // workgroups
     const double waves = e.wg / 64;
-    int64_t best = EVAL_FOLD;
+    int64_t best = g.nb;
     double least = 1e300;
     for (int64_t bc = EVAL_FOLD;; bc += EVAL_FOLD * (1 + bc / (16 * EVAL_FOLD))) {
         const int64_t nch = (g.nb + bc - 1) / bc;
+        if (nch > most) continue;  // one chunk (bc >= nb) never is
         const int64_t k = (nch * per_chunk + 255) / 256;  // workgroups on the fullest CU
         const double per_simd = (double)k * waves / 4.0;
         const double busy = 0.1 * per_simd * (double)bc * (1.0 + 0.4 / (per_simd < 8.0 ? per_simd : 8.0));
@@ -2705,7 +2712,7 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
     // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
     // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
     e.folded = !e.small && !indep && large && g.P >= 2 && wave_blocks >= 65536.0;
-    int64_t bc;
+    int64_t bc, ref_chunks = 0;
     if (bc_override > 0) {
         bc = bc_override;
     } else {
@@ -2718,7 +2725,10 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
         if (nch < 1) nch = 1;
         bc = (g.nb + nch - 1) / nch;
         if (bc < EVAL_FOLD) bc = EVAL_FOLD;
-        if (large) bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e);
+        if (large) {
+            ref_chunks = (g.nb + bc - 1) / bc;
+            bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e, ref_chunks);
+        }
         // a small run: chunks short enough that the fused loop's workgroup
         // takes every (pair, chunk) item at once
         if ((int64_t)g.P * g.nb <= (int64_t)FUSED_WG * EVAL_FOLD) {
@@ -2731,10 +2741,13 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
     e.bc = bc;
     e.nchunks = (g.nb + bc - 1) / bc;
     e.small = e.small && e.nchunks <= SMALL_MAX_CHUNKS;  // its partials in LDS, at most four passes over the chunks
+    // At least what the smaller runs' plan takes, so that the static scratch
+    // holds the same evaluates under either (one launch uses none of it).
+    e.partial_chunks = ref_chunks > 0 && e.small ? ref_chunks : std::max(ref_chunks, e.nchunks);
     return e;
 }
 
-int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e) { return e.nchunks * g.R * (int64_t)g.N; }
+int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e) { return e.partial_chunks * g.R * (int64_t)g.N; }
 
 hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m1, float* v,
                        float* best_x, hipStream_t s)
