@@ -405,7 +405,8 @@ bool kernel_can_store(const es_handle* h, const void* p)
 
 // Several state arrays out (entries with a null dst are skipped): one launch
 // for all of them, or a copy command each where a destination is not plain
-// memory of the handle's device.
+// memory of the handle's device or two of them overlap (the last one then stays,
+// as copies in order leave it).
 es_status copy_out(es_handle* h, int64_t rows, int64_t D, std::initializer_list<std::pair<float*, const float*>> arrays)
 {
     float* dst[EXPORT_MAX];
@@ -418,6 +419,12 @@ es_status copy_out(es_handle* h, int64_t rows, int64_t D, std::initializer_list<
         src[n++] = a.second;
         kernel = kernel && kernel_can_store(h, a.first);
     }
+    const uintptr_t bytes = (uintptr_t)rows * (uintptr_t)D * 4;
+    for (int k = 1; k < n; ++k)
+        for (int j = 0; j < k; ++j) {
+            const uintptr_t x = reinterpret_cast<uintptr_t>(dst[j]), y = reinterpret_cast<uintptr_t>(dst[k]);
+            kernel = kernel && (x < y ? y - x : x - y) >= bytes;
+        }
     if (n > 1 && kernel) {
         ES_HIP(h, launch_export_rows(rows, D, n, dst, src, h->stream), "copy out");
         return ES_OK;

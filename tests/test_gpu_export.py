@@ -32,3 +32,15 @@ def test_state_and_strategy_state_out(D, R):
     assert torch.equal(alone, src[1]) and t.value == 7
     sg, ve = es.strategy_state(velocity=True)
     assert torch.equal(sg, src[3].abs()) and torch.equal(ve, src[4])
+
+
+def test_overlapping_destinations_keep_the_last_array():
+    import paper_2212_04180_amd as P
+    es = P.ES(P.ESConfig(num_dims=70001, popsize=6, seed=3, problem=P.PROB_SPHERE))
+    src = [torch.full((1, 70001), v, device="cuda") for v in (1.0, 2.0, 3.0)]
+    es.set_state(*src, 7)
+    buf = torch.zeros(70001 + 5000, device="cuda")
+    at = [ctypes.c_void_p(buf[k:].data_ptr()) for k in (0, 5000, 0)]
+    es._check(P.lib().es_get_state(es._h, *at, None))
+    got = buf.cpu().numpy()
+    assert np.all(got[:70001] == 3.0) and np.all(got[70001:] == 2.0)
