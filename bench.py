@@ -35,19 +35,29 @@ MLP_FLOPS_PER_MEMBER = 2 * 256 * (64 * 256 + 256 * 256 + 256 * 16)
 # relative to v_fma_f32 (1): v_mad_u64_u32, v_mul_hi/lo_u32, v_cvt_*, fp64
 # fma/add 2; v_log/v_sqrt/v_sin/v_cos 4; bitwise, shifts, fp32 add/mul/fma 1.
 #   Philox-4x32-10: 20 x 32x32->64 product (2) + 20 x three-input xor (1)      = 60
-#   Box-Muller: 4 shift + 4 cvt (2) + 4 x 2^-24 scale (the radius words'
-#     +1 folded into their scale as one fma) + 2 log2 (4) + 2 x (-2 ln 2)
-#     + 2 sqrt (4) + 2 sin (4) + 2 cos (4) + 4 (r * trig)                      = 54
+#   Box-Muller: 4 shift + 4 x scale (the radius words' +1 folded into
+#     theirs as one fma; the words are read as subnormals, not converted)
+#     + 2 log2 (4) + 2 x (-2 ln 2) + 2 sqrt (4) + 2 sin (4) + 2 cos (4)
+#     + 4 (r * trig)                                                           = 46
 #   members (both signs): 8 fma for x plus the problem's terms, and the fold
 #     of each member's fp32 block sum into fp64 (2 x (cvt 2 + add 2) = 8):
 #     sphere 8 squares -> 24; shifted sphere 8 sub + 8 squares -> 32;
 #     Rosenbrock 6 ops x 4 terms x 2 -> 64; Rastrigin 8 ops x 8 -> 80 (fract of
 #     |x| (1), cos (4), -a cos (1), x^2 + that (1), the add (1)).
-PHILOX_BM = 60 + 54
+PHILOX_BM = 60 + 46
 EVAL_SLOTS_PER_PAIR_BLOCK = {"sphere": PHILOX_BM + 24, "shifted_sphere": PHILOX_BM + 32,
                              "rosenbrock": PHILOX_BM + 64, "rastrigin": PHILOX_BM + 80}
-# tell: Philox + Box-Muller + 4 fma (w * eps) + the fp64 fold every 16 pairs
+# Large evaluates with antithetic pairs and one sigma a run keep a pair's even
+# and odd sums (k_eval_fold): Philox and the four shifts, scales and eight
+# transcendentals (100), then per block and with the fp64 folds and the row
+# sums (2): sphere 2 x (add, mul, 2 fma); Rosenbrock 2 x (mul, fma) + 4 x 7;
+# Rastrigin 2 x (mul, fma) + 4 x (mul, fract, sin (4), cos (4), 3 fma).
+FOLD_SLOTS_PER_PAIR_BLOCK = {"sphere": 110, "shifted_sphere": 110, "rosenbrock": 134, "rastrigin": 158}
+# tell: Philox + Box-Muller + 4 fma (w * eps) + the fp64 fold every 16 pairs;
+# large runs' single sum weighs the radius instead of the normals (4 fewer)
 TELL_SLOTS_PER_PAIR_BLOCK = PHILOX_BM + 4 + 1
+TELL_LARGE_SAVES = 4
+LARGE_FROM = 1 << 18  # pair-blocks of a run, EVAL_LARGE_FROM of the kernels
 # es_run's code paths (es_run_path); where a loop's gradient reads the
 # normals its evaluate kept in LDS (es_run_path's keeps_normals), its work per
 # pair-block omits one Philox block and Box-Muller
@@ -257,7 +267,11 @@ def time_workload(P, torch, name, K, W, path, dev, stream, copy_mib=0):
     if prob is not None and path == "percall":
         vec = cfg.strategy != P.STRAT_OPENAI_ES
         eval_slots = EVAL_SLOTS_PER_PAIR_BLOCK[prob] + (EVAL_VEC_EXTRA if vec else 0)
-        tell_slots = TELL_SLOTS_PER_PAIR_BLOCK + (TELL_TWO_EXTRA if vec else 0)
+        large = (N // 2) * ((D + 3) // 4) > LARGE_FROM
+        folded = large and not vec and pair_blocks >= 65536 * 64 and N >= 128 and pair_blocks > 6e6
+        if folded:
+            eval_slots = FOLD_SLOTS_PER_PAIR_BLOCK[prob]
+        tell_slots = TELL_SLOTS_PER_PAIR_BLOCK + (TELL_TWO_EXTRA if vec else -TELL_LARGE_SAVES if large else 0)
         tell_items = pair_blocks
         if cfg.strategy == P.STRAT_SEP_CMA:
             # independent members: a second Philox block and Box-Muller per
@@ -273,7 +287,8 @@ def time_workload(P, torch, name, K, W, path, dev, stream, copy_mib=0):
                 "unit": "T VALU lane-op slots/s", "frac": achieved / VALU_PEAK,
                 "traffic": profiled_traffic(name),
                 "traffic_copy_scaled": profiled_traffic(name, "eval_hbm_bytes_per_launch"),
-                "kernel": "k_eval_bbob (fused sample+evaluate)",
+                "kernel": "k_eval_fold (fused sample+evaluate, a pair's even and odd sums)" if folded
+                          else "k_eval_bbob or k_eval_small (fused sample+evaluate)",
                 "kernel_ms": eval_ms, "slots_per_pair_block": eval_slots,
                 "pair_blocks_per_launch": pair_blocks,
                 "issued_instructions_per_pair_block": issued,
@@ -293,7 +308,7 @@ def time_workload(P, torch, name, K, W, path, dev, stream, copy_mib=0):
     if cfg.problem == P.PROB_MLP and path == "percall":
         flops = R * N * MLP_FLOPS_PER_MEMBER
         achieved = flops / (eval_ms * 1e-3)
-        tell_achieved = pair_blocks * TELL_SLOTS_PER_PAIR_BLOCK / (rest_ms * 1e-3)
+        tell_achieved = pair_blocks * (TELL_SLOTS_PER_PAIR_BLOCK - TELL_LARGE_SAVES) / (rest_ms * 1e-3)
         roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": BF16_MFMA_PEAK / 1e12, "unit": "TFLOP/s",
                 "frac": achieved / BF16_MFMA_PEAK, "traffic": None,
                 "kernel": "k_eval_mlp (the bf16 MFMA forward of every member)",
