@@ -396,6 +396,16 @@ int64_t es_generation(const es_handle* h);
  * the same bits either way. */
 int32_t es_run_path(const es_handle* h, int32_t* keeps_normals);
 
+/* The kernels that evaluate a configuration's built-in problem (host value;
+ * no device work; not defined by the paper): 1 = evaluate and reduction in
+ * one launch, 2 = two launches, each lane scoring its pair's two members,
+ * 3 = two launches, each lane summing what is even and what is odd in its
+ * pair's perturbation, 4 = the MLP forward; 0 for ES_PROB_NONE and for a cfg
+ * es_init would refuse.  partial_floats (NULL to skip) receives the floats of
+ * per-chunk partial sums between the two launches, [chunks][R][N] (0 where
+ * there are none). */
+int32_t es_eval_path(const es_config* cfg, int64_t* partial_floats);
+
 /* Message of the last failed call on h ("" if none); with h == NULL, the
  * message of the last failed es_init on this thread.  Never NULL. */
 const char* es_last_error(const es_handle* h);

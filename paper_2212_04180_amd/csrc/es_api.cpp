@@ -198,6 +198,18 @@ const char* validate(const es_config& c)
     return nullptr;
 }
 
+Geometry geometry_of(const es_config& c)
+{
+    Geometry g;
+    g.D = c.num_dims;
+    g.nb = (g.D + 3) / 4;
+    g.Dp = 4 * g.nb;
+    g.N = c.popsize;
+    g.P = c.popsize / 2;
+    g.R = c.num_runs;
+    return g;
+}
+
 // Sep-CMA-ES parent count: max(1, floor(elite_ratio N)).
 int32_t cma_mu(const es_config& c)
 {
@@ -486,6 +498,17 @@ int32_t es_run_path(const es_handle* h, int32_t* keeps_normals)
     return path;
 }
 
+int32_t es_eval_path(const es_config* cfg, int64_t* partial_floats)
+{
+    if (partial_floats) *partial_floats = 0;
+    if (!cfg || validate(*cfg) || cfg->problem == ES_PROB_NONE) return 0;
+    if (cfg->problem == ES_PROB_MLP) return 4;
+    const Geometry g = geometry_of(*cfg);
+    const EvalPlan e = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy == ES_STRAT_SEP_CMA);
+    if (partial_floats) *partial_floats = e.small ? 0 : e.nchunks * g.R * (int64_t)g.N;
+    return e.small ? 1 : e.folded ? 3 : 2;
+}
+
 es_status es_init(const es_config* cfg, void* hip_stream, es_handle** out)
 {
     if (!cfg || !out) return init_fail(ES_ERR_ARG, "null argument");
@@ -495,13 +518,8 @@ es_status es_init(const es_config* cfg, void* hip_stream, es_handle** out)
     if (!h) return init_fail(ES_ERR_OOM, "host allocation failed");
     h->cfg = *cfg;
     h->stream = reinterpret_cast<hipStream_t>(hip_stream);
-    Geometry& g = h->g;
-    g.D = cfg->num_dims;
-    g.nb = (g.D + 3) / 4;
-    g.Dp = 4 * g.nb;
-    g.N = cfg->popsize;
-    g.P = cfg->popsize / 2;
-    g.R = cfg->num_runs;
+    h->g = geometry_of(*cfg);
+    const Geometry& g = h->g;
     h->plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy == ES_STRAT_SEP_CMA);
     // where es_run takes the fused loop (the rule of es_run), the per-call
     // gradient kernel sums in the fused loop's order, so both give the same bits
@@ -687,13 +705,7 @@ es_status es_eval_noalloc(const es_config* cfg, const float* mean, const float* 
     if (cfg->num_dims % 4 != 0 && cfg->num_runs != 1)
         return init_fail(ES_ERR_UNSUPPORTED, "several runs need num_dims % 4 == 0", kNoalloc);
     if (t < 0 || t > 0xFFFFFFFFll) return init_fail(ES_ERR_ARG, "t out of range", kNoalloc);
-    Geometry g;
-    g.D = cfg->num_dims;
-    g.nb = (g.D + 3) / 4;
-    g.Dp = 4 * g.nb;
-    g.N = cfg->popsize;
-    g.P = cfg->popsize / 2;
-    g.R = cfg->num_runs;
+    const Geometry g = geometry_of(*cfg);
     const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks, false);
     const int64_t need = eval_partial_elems(g, plan);
     if (need > (int64_t)NOALLOC_SCRATCH_FLOATS) {

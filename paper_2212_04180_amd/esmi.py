@@ -29,8 +29,8 @@ EXPORTS = ("es_init", "es_ask", "es_eval", "es_eval_timed", "es_eval_noalloc", "
            "es_get_best", "es_get_shaped", "es_get_grad", "es_set_hparams", "es_get_hparams",
            "es_get_strategy_state", "es_set_strategy_state", "es_get_penalty",
            "es_get_problem_data", "es_debug_noise",
-           "es_save_state", "es_load_state", "es_sync", "es_generation", "es_run_path", "es_last_error",
-           "es_status_string", "es_destroy")
+           "es_save_state", "es_load_state", "es_sync", "es_generation", "es_run_path", "es_eval_path",
+           "es_last_error", "es_status_string", "es_destroy")
 
 
 class EsError(RuntimeError):
@@ -181,6 +181,7 @@ def lib() -> ctypes.CDLL:
         "es_sync": (i32, [vp]),
         "es_generation": (i64, [vp]),
         "es_run_path": (i32, [vp, vp]),
+        "es_eval_path": (i32, [P(_Config), P(i64)]),
         "es_last_error": (ctypes.c_char_p, [vp]),
         "es_status_string": (ctypes.c_char_p, [i32]),
         "es_destroy": (None, [vp]),
@@ -215,6 +216,14 @@ def eval_noalloc(cfg: ESConfig, mean, sigma, t: int, problem_data=None, out=None
     if rc != ES_OK:
         raise EsError(rc, lib().es_last_error(None).decode())
     return out
+
+
+def eval_path(cfg: ESConfig):
+    """es_eval_path: (path, floats of partial sums) of the configuration's
+    evaluate; path 1 one launch, 2 member by member, 3 even and odd sums, 4 MLP."""
+    cs, n = cfg.cstruct(), ctypes.c_int64(0)
+    path = lib().es_eval_path(ctypes.byref(cs), ctypes.byref(n))
+    return int(path), int(n.value)
 
 
 class ES:
