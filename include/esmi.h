@@ -247,7 +247,10 @@ es_status es_ask(es_handle* h, float* x_out);
 
 /* evaluate (Sec. 2.1 step 2) with the configured built-in problem, fused
  * with the sampling: fitness_out device [R][N].  Requires a preceding es_ask
- * for this generation; ES_ERR_UNSUPPORTED for ES_PROB_NONE. */
+ * for this generation; ES_ERR_UNSUPPORTED for ES_PROB_NONE.  The fitness is
+ * that of the members es_ask hands out, to fp32's rounding in another order of
+ * sums (large runs: es_eval_path 3 sums the members before their rounding to
+ * fp32 where that rounding is below the fitness's). */
 es_status es_eval(es_handle* h, float* fitness_out);
 
 /* Timing aid, not an operation of the paper: es_eval that also times its

@@ -433,6 +433,21 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
 // lose digits) or the sums leave the range that squares of fp32 values have
 // room in, the lane's chunk is evaluated member by member instead, with
 // eval_chunk: the results keep their precision, infinities and NaN.
+//
+// The fitness is that of the member x = fl32(m +- b) that es_ask hands out,
+// while this kernel sums m +- b unrounded.  A dim's rounding is 2^-25.2 |x| on
+// average (rms), so together they move the shifted sphere's chunk sum f by
+// 2^-24.2 max|x| sqrt f or less, and Rosenbrock's by ten times that with
+// |x| + 2 x^2 for |x|.  A chunk is folded only where that is at most
+// 2^-24.2 sqrt(k) f with k the number of chunks, at most 256: the chunks'
+// roundings are independent, so that the member's fitness moves by no more than
+// its own fp32 rounding.  Near an optimum (|x - s| a hundredth of |x| and less) the
+// chunk goes member by member; the workgroup sees that from the staged rows,
+// before its first block, and so does not work twice.  Without this the fitness
+// was off by 5e-4 at 1e-6 from the shifted sphere's optimum; it costs 1 to 4% of the
+// kernel (shifted sphere D = 1e6: 812 -> 818 us per generation).  Rastrigin's
+// A cos terms have larger roundings of their own, and the sphere's dims are its
+// members': neither needs it.
 constexpr int FOLD_TILE_MIN = 256;  // dims staged at once, at least (else one per lane)
 
 template <int PROB, int SM>
@@ -440,17 +455,69 @@ struct FoldRows {
     static constexpr bool sphere = PROB == ES_PROB_SPHERE || PROB == ES_PROB_SHIFTED_SPHERE;
     static constexpr int terms = sphere ? 1 : 3;
     static constexpr int n = terms + (SM == SM_VEC ? 1 : 0);  // float rows of one tile, then a quarter row of block sums
+    static constexpr bool rounds = PROB == ES_PROB_SHIFTED_SPHERE || PROB == ES_PROB_ROSENBROCK;  // members' rounding shows
 };
+constexpr int FOLD_ROWS = EVAL_MAX_WG / 16;  // largest |x| of each 16 lanes, behind the tile
+
+// Sum over the wave in its last lane, and the maximum of values >= 0 as their bit
+// patterns (an integer maximum takes the exchange into its own instruction):
+// over 16 neighbouring lanes in all of them, over the wave in the last lane.
+template <int CTRL>
+__device__ __forceinline__ int dpp16(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_rows(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t max16(uint32_t v)
+{
+    v = max(v, (uint32_t)dpp16<0xB1>((int)v));         // quad_perm 1, 0, 3, 2
+    v = max(v, (uint32_t)dpp16<0x4E>((int)v));         // quad_perm 2, 3, 0, 1
+    v = max(v, (uint32_t)dpp16<0x141>((int)v));        // row_half_mirror
+    return max(v, (uint32_t)dpp16<0x140>((int)v));     // row_mirror
+}
+__device__ __forceinline__ uint32_t wave_max63(uint32_t v)
+{
+    v = max16(v);
+    v = max(v, (uint32_t)dpp_rows<0x142, 0xA>((int)v));     // row_bcast:15 into rows 1 and 3
+    return max(v, (uint32_t)dpp_rows<0x143, 0xC>((int)v));  // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ float wave_sum63(float v)
+{
+    v += __int_as_float(dpp16<0xB1>(__float_as_int(v)));
+    v += __int_as_float(dpp16<0x4E>(__float_as_int(v)));
+    v += __int_as_float(dpp16<0x141>(__float_as_int(v)));
+    v += __int_as_float(dpp16<0x140>(__float_as_int(v)));
+    v += __int_as_float(dpp_rows<0x142, 0xA>(__float_as_int(v)));
+    return v + __int_as_float(dpp_rows<0x143, 0xC>(__float_as_int(v)));
+}
+__device__ __forceinline__ float last_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// The members' rounding against the root of the chunk's sum, from its largest |x|.
+template <int PROB>
+__device__ __forceinline__ float fold_reach(float x)
+{
+    return PROB == ES_PROB_ROSENBROCK ? 10.0f * fmaf(2.0f * x, x, x) : x;
+}
 
 constexpr int fold_tile(int wg) { return wg > FOLD_TILE_MIN ? wg : FOLD_TILE_MIN; }
 
 // What dim d contributes to the even sum by itself goes to q; t: its rows.
 // Rosenbrock: the term of dims d - 1 and d (d >= 1), scaled by 1 / 100.
+// reach: the bits of the largest |x| so far (|eps| <= 5.77; a scalar sigma's share is added
+// once for all dims).
 template <int PROB, int SM>
 __device__ __forceinline__ void fold_rows(const float* __restrict__ mr, const float* __restrict__ pdata, int64_t d,
-                                          float ra, float t[3], float& q)
+                                          float ra, float g, float t[3], float& q, uint32_t& reach)
 {
     const float m = mr[d];
+    if constexpr (FoldRows<PROB, SM>::rounds) reach = max(reach, __float_as_uint(SM == SM_VEC ? fmaf(5.78f, g, fabsf(m)) : fabsf(m)));
     if constexpr (FoldRows<PROB, SM>::sphere) {
         const float a = PROB == ES_PROB_SHIFTED_SPHERE ? m - pdata[d] : m;
         t[0] = SM == SM_VEC ? 2.0f * a : a;
@@ -468,6 +535,23 @@ __device__ __forceinline__ void fold_rows(const float* __restrict__ mr, const fl
         t[1] = -2.0f * mi;
         t[2] = -0.01f * o;
         q = 0.01f * o * o;
+    }
+}
+
+// Half of what the block of a staged dim 4 l adds to a member's sum on average,
+// as if its other dims were like it.
+template <int PROB, int SM>
+__device__ __forceinline__ float fold_level(const float* rows, int32_t TD, int32_t l, float sigma)
+{
+    using FR = FoldRows<PROB, SM>;
+    const float g = SM == SM_VEC ? (float)(1.0 / SQRT_2LN2) * rows[FR::terms * TD + 4 * l] : sigma, g2 = g * g;
+    const float t0 = rows[4 * l];
+    if constexpr (FR::sphere) {
+        const float a = SM == SM_VEC ? 0.5f * t0 : t0;
+        return 2.0f * fmaf(a, a, g2);
+    } else {
+        const float t1 = rows[TD + 4 * l], e = t0 - g2;
+        return 200.0f * fmaf(e, e, g2 * fmaf(2.0f, g2, fmaf(t1, t1, 1.0f)));
     }
 }
 
@@ -528,7 +612,7 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
     int32_t n_pg, const float* __restrict__ hp, float ra, const float* __restrict__ svec)
 {
     using FR = FoldRows<PROB, SM>;
-    extern __shared__ __align__(16) float rows[];  // [FR::n][TD] | block sums [TD / 4]
+    extern __shared__ __align__(16) float rows[];  // [FR::n][TD] | block sums [TD / 4] | reach [FOLD_ROWS]
     const int32_t r = blockIdx.y;
     const float sigma = hp[r];
     const uint32_t w = blockIdx.x;
@@ -548,7 +632,7 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
     // the row's first group, whose first dim has none before it)
     const int64_t nfull = D / 4 < b1 ? D / 4 : b1;
     const int64_t f0 = PROB == ES_PROB_ROSENBROCK && b0 == 0 ? EVAL_FOLD : b0;
-    const int64_t f1 = nfull > f0 ? f0 + (nfull - f0) / EVAL_FOLD * EVAL_FOLD : f0;
+    int64_t f1 = nfull > f0 ? f0 + (nfull - f0) / EVAL_FOLD * EVAL_FOLD : f0;
     const int32_t wg = (int32_t)blockDim.x, TD = fold_tile(wg);
 
     const double kbd = -TWO_LN2 * (double)sigma * (double)sigma;
@@ -564,12 +648,16 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
         bl = (SM == SM_VEC ? gr[4 * f0 - 1] : sigma) * e[3];
     }
     double even = PROB == ES_PROB_ROSENBROCK ? 0.01 * (double)bl * (double)bl : 0.0, odd = 0.0;
+    uint32_t* lim = reinterpret_cast<uint32_t*>(rows + FR::n * TD + TD / 4);
+    const float per_k = __builtin_amdgcn_rcpf((float)(int32_t)(nchunks < 256 ? nchunks : 256));
+    float need = 0.f;  // what the members' sums must reach for the chunk to be folded
     for (int64_t bt = f0; bt < f1; bt += TD / 4) {
         const int32_t nbt = (int32_t)(f1 - bt < TD / 4 ? f1 - bt : TD / 4);
         if (bt > f0) __syncthreads();  // every lane is done with the previous tile
+        uint32_t reach = 0;
         for (int32_t i = (int32_t)threadIdx.x; i < 4 * nbt; i += wg) {
             float tv[3] = {0.f, 0.f, 0.f}, q;
-            fold_rows<PROB, SM>(mr, pdata, 4 * bt + i, ra, tv, q);
+            fold_rows<PROB, SM>(mr, pdata, 4 * bt + i, ra, SM == SM_VEC ? gr[4 * bt + i] : sigma, tv, q, reach);
 #pragma unroll
             for (int k = 0; k < FR::terms; ++k) rows[k * TD + i] = tv[k];
             if constexpr (SM == SM_VEC) rows[FR::terms * TD + i] = (float)(SQRT_2LN2 * (double)gr[4 * bt + i]);
@@ -578,7 +666,27 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
             q += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(q), 0x4E, 0xF, 0xF, false));
             if ((i & 3) == 0) rows[FR::n * TD + (i >> 2)] = (float)((double)q * qs);
         }
+        if constexpr (FR::rounds) {
+            reach = max16(reach);
+            if ((threadIdx.x & 15) == 0) lim[threadIdx.x >> 4] = reach;
+        }
         __syncthreads();
+        if constexpr (FR::rounds) {
+            const int32_t l = (int32_t)threadIdx.x & 63;
+            const float x = fold_reach<PROB>(last_lane(__uint_as_float(wave_max63(l < (wg >> 4) ? lim[l] : 0u))) +
+                                             (SM == SM_VEC ? 0.f : 5.78f * sigma));
+            need = fmaxf(need, x * x * per_k);
+            if (bt == f0) {
+                // the chunk's mean sum from one dim of each of up to 64 blocks
+                const int32_t ns = nbt < 64 ? nbt : 64;
+                float v = 0.f;
+                if (l < ns) v = fold_level<PROB, SM>(rows, TD, l, sigma);
+                if (!(need * (float)ns <= last_lane(wave_sum63(v)) * (float)(int32_t)(f1 - f0))) {
+                    f1 = f0;  // no block is folded
+                    break;
+                }
+            }
+        }
         for (int32_t i = 0; i < nbt; i += EVAL_FOLD) {
             const float4 q4 = *reinterpret_cast<const float4*>(rows + FR::n * TD + i);
             float ev = (q4.x + q4.y) + (q4.z + q4.w), es = 0.f, od = 0.f;
@@ -612,7 +720,8 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
         span = even;
     }
     double accp = even + odd, accm = even - odd;
-    const bool whole = fabs(odd) <= 0.9375 * span && span < 1e30;
+    bool whole = fabs(odd) <= 0.9375 * span && span < 1e30;
+    if constexpr (FR::rounds) whole = whole && (double)need <= fmin(accp, accm);
     // member by member: the folded blocks of a lane that needs it, then the
     // blocks before and after them
     for (int part = 0; part < 3; ++part) {
@@ -2812,7 +2921,7 @@ hipError_t launch_ask(const Geometry& g, const es_config& c, uint32_t t, const f
 template <int PROB, int SM>
 constexpr uint32_t fold_lds_bytes(int wg)
 {
-    return (uint32_t)(sizeof(float) * (FoldRows<PROB, SM>::n * fold_tile(wg) + fold_tile(wg) / 4));
+    return (uint32_t)(sizeof(float) * (FoldRows<PROB, SM>::n * fold_tile(wg) + fold_tile(wg) / 4 + FOLD_ROWS));
 }
 
 hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPlan& e, uint32_t t,

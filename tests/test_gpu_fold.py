@@ -95,3 +95,51 @@ def test_overflow_and_nan_as_member_by_member(value, problem, strategy):
     ok = np.isfinite(fr)
     np.testing.assert_array_equal(f[~ok], fr[~ok])
     np.testing.assert_allclose(f[ok], fr[ok], rtol=1e-5)
+
+
+def _exact(P, cfg, x, shift):
+    """Fitness of the fp32 members x [N][D] in 64 bits."""
+    f = torch.empty(len(x), dtype=torch.float64, device="cuda")
+    for j in range(0, len(x), 64):
+        y = x[j:j + 64].double()
+        if cfg.problem == P.PROB_ROSENBROCK:
+            f[j:j + 64] = (100 * (y[:, 1:] - y[:, :-1] ** 2) ** 2 + (1 - y[:, :-1]) ** 2).sum(1)
+        else:
+            f[j:j + 64] = ((y - shift) ** 2).sum(1)
+    return f
+
+
+@pytest.mark.parametrize("strategy", ["openai", "pgpe"])
+@pytest.mark.parametrize("problem", ["sphere", "shifted_sphere", "rosenbrock"])
+@pytest.mark.parametrize("where", ["near", "near and far", "one dim far", "far"])
+def test_fitness_is_that_of_the_members_handed_out(where, problem, strategy):
+    """Down to perturbations below the last place of the mean, f is f of the fp32 members.  4 x 2^-24 of f: its
+    own rounding, the sums' (16 dims in fp32), what is left of the members', and the normals' squares by their
+    radius instead of cosine and sine.  Where one dim holds the sum its 16 dims' roundings do not average: 16 x."""
+    P = _P()
+    for sigma in (1e-1, 1e-2, 3e-3, 1e-3, 1e-4, 1e-5, 1e-6, 1e-7):
+        cfg = _cfg(problem, 131075, 130, 1, strategy, sigma=sigma)
+        assert P.eval_path(cfg)[0] == 3
+        es = P.ES(cfg)
+        gen = torch.Generator("cuda").manual_seed(7)
+        D = cfg.num_dims
+        shift = es.problem_data() if problem == "shifted_sphere" else torch.zeros(D, device="cuda")
+        off = torch.randn(1, D, generator=gen, device="cuda")
+        scale = torch.full((1, D), sigma, device="cuda")
+        if where == "near and far":
+            scale[:, D // 3:] = 1.0
+        elif where == "one dim far":
+            scale[:, 70001] = 30.0
+        elif where == "far":
+            scale[:] = 1.0
+        m = ((1.0 if problem == "rosenbrock" else shift) + scale * off).float().reshape(1, D)
+        z = torch.zeros_like(m)
+        es.set_state(m, z, z, 0)
+        if strategy == "pgpe":
+            es.set_strategy_state(sigma * (0.5 + torch.rand(1, D, generator=gen, device="cuda")))
+        x = es.ask(materialize=True)[0]
+        ref = _exact(P, cfg, x, shift.double())
+        err = float(((es.eval()[0].double() - ref).abs() / ref).max())
+        print(where, problem, strategy, sigma, f"{err:.2e}", flush=True)
+        assert err <= (16 if where == "one dim far" else 4) * 2.0 ** -24, (sigma, err)
+        es.close()
