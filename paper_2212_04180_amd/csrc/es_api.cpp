@@ -402,36 +402,41 @@ hipError_t copy_rows(const Geometry& g, float* dst, size_t dpitch, const float* 
     return hipSuccess;
 }
 
-// Whether a kernel of this handle can store to p as a copy command would:
-// device memory of the handle's own device, 4-byte aligned.
-bool kernel_can_store(const es_handle* h, const void* p)
+// Whether a kernel of this handle can store the bytes at p as a copy command
+// would: device memory of the handle's own device, 4-byte aligned, all within one
+// allocation (a copy command refuses what runs past its end, a kernel would not).
+bool kernel_can_store(const es_handle* h, void* p, size_t bytes)
 {
     if (reinterpret_cast<uintptr_t>(p) & 3) return false;
     hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != h->device ||
+        hipMemGetAddressRange(&base, &size, reinterpret_cast<hipDeviceptr_t>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == h->device;
+    const uintptr_t off = reinterpret_cast<uintptr_t>(p) - reinterpret_cast<uintptr_t>(base);
+    return off <= size && bytes <= size - off;
 }
 
 // Several state arrays out (entries with a null dst are skipped): one launch
 // for all of them, or a copy command each where a destination is not plain
-// memory of the handle's device or two of them overlap (the last one then stays,
-// as copies in order leave it).
+// memory of the handle's device with room for its array or two of them overlap
+// (the last one then stays, as copies in order leave it).
 es_status copy_out(es_handle* h, int64_t rows, int64_t D, std::initializer_list<std::pair<float*, const float*>> arrays)
 {
     float* dst[EXPORT_MAX];
     const float* src[EXPORT_MAX];
+    const size_t bytes = (size_t)rows * (size_t)D * 4;
     int n = 0;
     bool kernel = true;
     for (const auto& a : arrays) {
         if (!a.first) continue;
         dst[n] = a.first;
         src[n++] = a.second;
-        kernel = kernel && kernel_can_store(h, a.first);
+        kernel = kernel && kernel_can_store(h, a.first, bytes);
     }
-    const uintptr_t bytes = (uintptr_t)rows * (uintptr_t)D * 4;
     for (int k = 1; k < n; ++k)
         for (int j = 0; j < k; ++j) {
             const uintptr_t x = reinterpret_cast<uintptr_t>(dst[j]), y = reinterpret_cast<uintptr_t>(dst[k]);

@@ -44,3 +44,29 @@ def test_overlapping_destinations_keep_the_last_array():
     es._check(P.lib().es_get_state(es._h, *at, None))
     got = buf.cpu().numpy()
     assert np.all(got[:70001] == 3.0) and np.all(got[70001:] == 2.0)
+
+
+def test_destination_shorter_than_its_array_is_refused():
+    # the runtime's copy refuses an array that runs past its destination's
+    # allocation; so does the call with several destinations (the allocation's
+    # page holds the array all the same)
+    import paper_2212_04180_amd as P
+    es = P.ES(P.ESConfig(num_dims=512, popsize=6, seed=3, problem=P.PROB_SPHERE))
+    src = [torch.full((1, 512), v, device="cuda") for v in (1.0, 2.0, 3.0)]
+    es.set_state(*src, 7)
+    L = P.lib()
+    L.hipMalloc.argtypes, L.hipFree.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t], [ctypes.c_void_p]
+    short = ctypes.c_void_p()
+    assert L.hipMalloc(ctypes.byref(short), 1024) == 0
+    out = torch.zeros(2, 512, device="cuda")
+    at = [ctypes.c_void_p(out[0].data_ptr()), short, ctypes.c_void_p(out[1].data_ptr())]
+    assert L.es_get_state(es._h, None, short, None, None) == -3  # alone: the copy's own refusal
+    L.hipGetLastError()
+    assert L.es_get_state(es._h, *at, None) == -3
+    assert b"copy out" in L.es_last_error(es._h)
+    L.hipGetLastError()
+    torch.cuda.synchronize()
+    assert torch.all(out[0] == 1.0) and torch.all(out[1] == 0.0)
+    st = es.get_state()
+    assert all(torch.equal(st[k], x) for k, x in zip(("m", "m1", "v"), src))
+    assert L.hipFree(short) == 0
