@@ -61,8 +61,9 @@ hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m
                        float* best_x, hipStream_t s);
 hipError_t launch_problem_data(const Geometry& g, const es_config& c, float* pdata, hipStream_t s);
 hipError_t launch_fill_rows(const Geometry& g, float* p, float value, hipStream_t s);  // [R][Dp], padding 0
-// State rows (row stride 4 ceil(D / 4), 16-byte aligned) into dense [rows][D]
-// arrays (4-byte aligned device memory), n <= EXPORT_MAX at once.
+// State rows (row stride 4 ceil(D / 4), 16-byte aligned; the last row's padding
+// is not read and may be absent) into dense [rows][D] arrays (4-byte aligned
+// device memory), n <= EXPORT_MAX at once.
 constexpr int EXPORT_MAX = 4;
 struct ExportArgs {
     float* dst[EXPORT_MAX];

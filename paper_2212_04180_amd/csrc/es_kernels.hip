@@ -2715,29 +2715,25 @@ __global__ void k_fill_rows(float* __restrict__ p, float value, int64_t D, int64
 // Up to EXPORT_MAX arrays out of the state's padded rows [R][4 nb] into dense
 // [R][D] ones, one launch for all of them (blockIdx.y): a copy command per
 // array costs a launch of its own, 2-5 us each at a few MB.  Lane = four dims;
-// a dense row starts on a 4-byte boundary.
+// a dense row starts on a 4-byte boundary.  Nothing beyond a row's D words is
+// read: a run's weights and ranks are one row without padding.
 __global__ __launch_bounds__(256) void k_export_rows(ExportArgs a)
 {
     const float* __restrict__ src = a.src[blockIdx.y];
     float* __restrict__ dst = a.dst[blockIdx.y];
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.total; i += (int64_t)gridDim.x * 256) {
-        const float4 v = *reinterpret_cast<const float4*>(src + 4 * i);
         int64_t b = i, o = 4 * i;
         if (a.rows > 1) {
             const int64_t r = a.total >> 32 ? i / a.nb : (int64_t)((uint32_t)i / (uint32_t)a.nb);
             b = i - r * a.nb;
             o = r * a.D + 4 * b;
         }
-        const float e[4] = {v.x, v.y, v.z, v.w};
         if (4 * b + 4 <= a.D) {
-            float4u u;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = e[k];
-            *reinterpret_cast<float4u*>(dst + o) = u;
+            const float4 v = *reinterpret_cast<const float4*>(src + 4 * i);
+            *reinterpret_cast<float4u*>(dst + o) = float4u{v.x, v.y, v.z, v.w};
         } else {
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                if (4 * b + k < a.D) dst[o + k] = e[k];
+            // the row's own words only: a single row need not be padded
+            for (int64_t k = 4 * b; k < a.D; ++k) dst[o + k - 4 * b] = src[4 * i + k - 4 * b];
         }
     }
 }

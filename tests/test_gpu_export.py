@@ -70,3 +70,24 @@ def test_destination_shorter_than_its_array_is_refused():
     st = es.get_state()
     assert all(torch.equal(st[k], x) for k, x in zip(("m", "m1", "v"), src))
     assert L.hipFree(short) == 0
+
+
+@pytest.mark.parametrize("N,R", [(2, 1), (6, 1), (6, 3), (10, 2), (1030, 1), (70002, 1)])
+def test_weights_and_ranks_out(N, R):
+    # one row of N R words without padding: sizes of both remainders, each
+    # array as it reads by itself, nothing written beyond it
+    import paper_2212_04180_amd as P
+    es = P.ES(P.ESConfig(num_dims=5, popsize=N, num_runs=R, seed=3, problem=P.PROB_NONE))
+    es.ask()
+    es.tell(torch.randn(R, N, device="cuda"))
+    L, buf = P.lib(), torch.full((4, N * R + 3), -9, dtype=torch.int32, device="cuda")
+    at = [ctypes.c_void_p(buf[k][1:].data_ptr()) for k in range(4)]
+    es._check(L.es_get_shaped(es._h, at[0], at[1]))
+    es._check(L.es_get_shaped(es._h, at[2], None))
+    es._check(L.es_get_shaped(es._h, None, at[3]))
+    got = buf.cpu().numpy()
+    np.testing.assert_array_equal(got[0], got[2])
+    np.testing.assert_array_equal(got[1], got[3])
+    assert np.all(got[:, 0] == -9) and np.all(got[:, 1 + N * R:] == -9)
+    for r in range(R):
+        np.testing.assert_array_equal(np.sort(got[1, 1 + r * N:1 + (r + 1) * N]), np.arange(N))
