@@ -2748,35 +2748,44 @@ int grid_for(int64_t n, int threads)
 
 // ---------------------------------------------------------------------------
 // Blocks per evaluate chunk of a large run: the least estimated time over
-// whole groups of EVAL_FOLD blocks.  The estimate (us): the workgroups of the
-// fullest CU, at 0.1 us for four waves' block (58 instructions, one per four
-// cycles and SIMD) and more with few waves per SIMD, or one
-// wave's chain of blocks; and 4 ns per chunk for its start and its place in the
-// reduction's chain of loads.  Evaluate with its reduction in us, at 24576
-// waves (the smaller runs' plan) / at this rule's chunk: 40,528 dims x 1096
-// members 46 / 24, 200,000 x 64 57 / 20, 50,001 x 510 30 / 16, 100,001 x 510 x 2
-// runs 40 / 35, 250,003 x 1000 73 / 66, 3000 x 2048 x 3 15.3 / 12.7, 1e6 x 2048
-// 411 / 411.
+// whole groups of EVAL_FOLD blocks.  The estimate (us): the waves of the fullest
+// SIMD, at a block's time each (0.1 us for k_eval_fold, 60 instructions of four
+// cycles; 0.14 and 0.25 for k_eval_bbob's pairs and independent members), more
+// with few waves per SIMD, a start-up of half a block (the staged tile: two), and
+// the uneven end of few workgroups; or one wave's chain of blocks; and 4 ns per
+// chunk in the reduction's chain of loads with the partials' way through memory.
+// Chunks are dealt to the XCDs, so the fullest CU is one of the XCD with
+// ceil(chunks / 8) of them (11 chunks keep five of eight XCDs half idle: 8200
+// dims x 410 members x 186 runs 255 us, at 24 chunks 171), and a workgroup of
+// two waves sits on one SIMD (1e6 x 256 x 2 runs: 138 us at 14 workgroups a CU,
+// 126 at 12 and at 16).  Evaluate with its
+// reduction in us, at 24576 waves (the smaller runs' plan) / at this rule's chunk,
+// shifted sphere: 50,001 dims x 510 members x 4 runs 45 / 34, 250,003 x 1000 88 /
+// 70, 1e6 x 2048 530 / 411, 1100 x 4096 x 100 151 / 131, 8200 x 410 x 186 262 / 201,
+// 1222 x 10,580 x 153 2377 / 1970, 131,072 x 130 77 / 24 (the first column is
+// k_eval_bbob's).
 //
 // The partials stay within the smaller runs' plan's (ref_chunks) or the static
 // scratch, whichever is larger: the estimate alone would take gigabytes for
 // many runs or dimensions (94 runs of 12,788 members in 1.7e6 dims: 8.7 GB).
-static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e, int64_t ref_chunks)
+static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e, int64_t ref_chunks, bool indep)
 {
     const int64_t members = g.R * (int64_t)g.N;
     const int64_t most = std::max<int64_t>(ref_chunks, (int64_t)NOALLOC_SCRATCH_FLOATS / members);
     const int64_t per_chunk = (int64_t)e.n_pg * g.R;  // workgroups
-    const double waves = e.wg / 64;
+    const int64_t waves = e.wg / 64;
+    const double block_us = e.folded ? 0.1 : indep ? 0.25 : 0.14, start = e.folded ? 2.0 : 0.5;
     int64_t best = g.nb;
     double least = 1e300;
     for (int64_t bc = EVAL_FOLD;; bc += EVAL_FOLD * (1 + bc / (16 * EVAL_FOLD))) {
         const int64_t nch = (g.nb + bc - 1) / bc;
         if (nch > most) continue;  // one chunk (bc >= nb) never is
-        const int64_t k = (nch * per_chunk + 255) / 256;  // workgroups on the fullest CU
-        const double per_simd = (double)k * waves / 4.0;
-        const double busy = 0.1 * per_simd * (double)bc * (1.0 + 0.4 / (per_simd < 8.0 ? per_simd : 8.0));
-        const double chain = 0.15 * (double)bc;
-        const double us = (busy > chain ? busy : chain) + 0.0042 * (double)nch;
+        const int64_t k = ((nch + 7) / 8 * per_chunk + 31) / 32;  // workgroups on the fullest CU
+        const int64_t on_simd = waves == 2 ? (k + 3) / 4 * 2 : k < 3 ? k * ((waves + 3) / 4) : (k * waves + 3) / 4;
+        const double per_simd = (double)on_simd;
+        const double busy = block_us * (per_simd * ((double)bc + start) * (1.0 + 0.4 / std::min(per_simd, 8.0)) +
+                                        0.8 * (double)bc / (double)k);
+        const double us = std::max(busy, 1.5 * block_us * (double)bc) + (double)nch * (0.0042 + 1.6e-6 * (double)members);
         if (us < least) {
             least = us;
             best = bc;
@@ -2832,7 +2841,7 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
         if (bc < EVAL_FOLD) bc = EVAL_FOLD;
         if (large) {
             ref_chunks = (g.nb + bc - 1) / bc;
-            bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e, ref_chunks);
+            bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e, ref_chunks, indep);
         }
         // a small run: chunks short enough that the fused loop's workgroup
         // takes every (pair, chunk) item at once

@@ -1,5 +1,8 @@
 """The evaluate's kernels per configuration, from es_eval_path (CPU only: a host
 rule).  The sizes of the GPU tests that name a kernel are checked against it there."""
+import math
+import random
+
 import pytest
 
 import paper_2212_04180_amd as P
@@ -25,3 +28,29 @@ def test_other_problems_and_refused_configurations():
     assert P.eval_path(P.ESConfig(num_dims=86544, popsize=64, problem=P.PROB_MLP,
                                   init=P.INIT_FANIN_NORMAL)) == (4, 0)
     assert P.lib().es_eval_path(None, None) == 0
+
+
+@pytest.mark.parametrize("D,N,R", [(8200, 410, 186), (1100, 4096, 100), (500, 16384, 16), (3696, 822, 268), (2100, 4096, 64),
+                                   (7157, 1776, 27), (1148, 1842, 213), (1_000_000, 2048, 1)])
+@pytest.mark.parametrize("strategy", [P.STRAT_OPENAI_ES, P.STRAT_SEP_CMA])
+def test_chunks_of_large_evaluates_fill_the_xcds(D, N, R, strategy):
+    # chunk c runs on XCD c mod 8: the fullest one holds at most a quarter more than the mean
+    path, partials = _path(D, N, R, strategy=strategy)
+    chunks = partials // (R * N)
+    assert path in (2, 3) and -(-chunks // 8) * 8 <= 1.25 * chunks, chunks
+
+
+def test_partials_of_large_evaluates_are_bounded():
+    # by the 24,576-wave plan of the smaller runs or the static scratch, whichever is larger
+    rng = random.Random(5)
+    for _ in range(20000):
+        D, N, R = (int(math.exp(rng.uniform(0.0, math.log(hi)))) for hi in (4e9, 200000, 65535))
+        N = 2 * max(1, N // 2)
+        if R * D > 6e10 or R * N * D > 1e15:
+            continue
+        waves = -(-min(-(-N // 2 // 64) * 64, 1024) // 64) * -(-(N // 2) // 1024) * R
+        nb = -(-D // 4)
+        bc = max(4, -(-nb // max(1, -(-24576 // waves))))
+        _, partials = _path(D, N, R, strategy=rng.choice((P.STRAT_OPENAI_ES, P.STRAT_PGPE, P.STRAT_SEP_CMA)))
+        if (N // 2) * nb > 1 << 18:
+            assert partials <= max(-(-nb // bc) * R * N, 1 << 22), (D, N, R)
