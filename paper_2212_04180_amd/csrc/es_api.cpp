@@ -509,7 +509,7 @@ int32_t es_eval_path(const es_config* cfg, int64_t* partial_floats)
     if (!cfg || validate(*cfg) || cfg->problem == ES_PROB_NONE) return 0;
     if (cfg->problem == ES_PROB_MLP) return 4;
     const Geometry g = geometry_of(*cfg);
-    const EvalPlan e = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy == ES_STRAT_SEP_CMA);
+    const EvalPlan e = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy);
     if (partial_floats) *partial_floats = e.small ? 0 : e.nchunks * g.R * (int64_t)g.N;
     return e.small ? 1 : e.folded ? 3 : 2;
 }
@@ -525,7 +525,7 @@ es_status es_init(const es_config* cfg, void* hip_stream, es_handle** out)
     h->stream = reinterpret_cast<hipStream_t>(hip_stream);
     h->g = geometry_of(*cfg);
     const Geometry& g = h->g;
-    h->plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy == ES_STRAT_SEP_CMA);
+    h->plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy);
     // where es_run takes the fused loop (the rule of es_run), the per-call
     // gradient kernel sums in the fused loop's order, so both give the same bits
     h->tell = tell_plan(g, fused_by_default(g, h->plan, *cfg), cfg->plan_tell_split);
@@ -711,7 +711,7 @@ es_status es_eval_noalloc(const es_config* cfg, const float* mean, const float* 
         return init_fail(ES_ERR_UNSUPPORTED, "several runs need num_dims % 4 == 0", kNoalloc);
     if (t < 0 || t > 0xFFFFFFFFll) return init_fail(ES_ERR_ARG, "t out of range", kNoalloc);
     const Geometry g = geometry_of(*cfg);
-    const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks, false);
+    const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy);
     const int64_t need = eval_partial_elems(g, plan);
     if (need > (int64_t)NOALLOC_SCRATCH_FLOATS) {
         std::snprintf(g_init_err, sizeof(g_init_err),

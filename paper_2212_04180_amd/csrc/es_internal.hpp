@@ -53,8 +53,7 @@ struct EvalPlan {
 // stored normals' blocks in 16 x 144 KB), so their sums need not follow the
 // loops' order.
 constexpr int64_t EVAL_LARGE_FROM = 1 << 18;
-// indep: independent members (Sep-CMA-ES) instead of antithetic pairs
-EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep);
+EvalPlan eval_plan(const Geometry& g, int64_t bc_override, int32_t strategy);
 int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e);  // floats
 
 hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m1, float* v,

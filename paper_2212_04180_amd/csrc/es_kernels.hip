@@ -789,8 +789,12 @@ __global__ __launch_bounds__(64 * RED_SLICES) void k_eval_reduce(const float* __
 // (both counter words vary across the lanes: 39 Philox instructions instead of
 // 33); the plan says where the line lies.
 constexpr int SMALL_WG = 256;
-constexpr int SMALL_MAX_CHUNKS = 4 * SMALL_WG;
+constexpr int SMALL_MAX_CHUNKS = 2 * SMALL_WG;
 constexpr int SMALL_MAX_PAIRS = 64;  // pairs per workgroup: 16 KB of slice sums, and every member a lane
+int32_t small_pairs(const Geometry& g, int64_t nchunks)
+{
+    return std::max(1, std::min(std::min((int32_t)(SMALL_WG / nchunks), SMALL_MAX_PAIRS), g.P));
+}
 template <int PROB, int SM>
 __global__ __launch_bounds__(SMALL_WG) void k_eval_small(const float* __restrict__ m, const float* __restrict__ pdata,
                                                          float* __restrict__ fit, uint64_t seed, uint32_t t, int64_t D,
@@ -2795,41 +2799,36 @@ static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e, int64_t r
     return best;
 }
 
-EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
+// Whether one launch pays over two for chunks of bc blocks: its wave-blocks
+// against two_launches (those of the other kernels), in the same unit.  A
+// workgroup's last pass leaves lanes idle, and the noise takes 39 Philox
+// instructions instead of 33 (1.15 of a block); the second launch is worth about
+// 32,000 wave-blocks (evaluate in us, two launches / one, Rastrigin, at excesses
+// of 21,000 2100 dims x 512 members x 8 runs 9.8 / 9.2; 29,000 2900 x 512 x 16 17.6
+// / 15.3; 42,000 2100 x 512 x 16 13.4 / 15.2; 97,000 4000 x 512 x 32 35.6 / 38.1).
+// More than two passes over a pair's chunks leave its few workgroups behind the
+// other kernels' many (64 members, 512 chunks 6.8 / 6.2, 563 7.4 / 8.2, 1024 8.4 /
+// 9.9).
+static bool one_launch_pays(const Geometry& g, int64_t bc, int64_t nchunks, double two_launches)
+{
+    if (nchunks > SMALL_MAX_CHUNKS) return false;
+    const int64_t pw = small_pairs(g, nchunks), passes = (pw * nchunks + SMALL_WG - 1) / SMALL_WG;
+    const int64_t waves = (g.P + pw - 1) / pw * g.R * (SMALL_WG / 64) * passes;
+    return 1.15 * (double)(waves * bc) - two_launches <= 32e3;
+}
+
+EvalPlan eval_plan(const Geometry& g, int64_t bc_override, int32_t strategy)
 {
     EvalPlan e;
+    const bool indep = strategy == ES_STRAT_SEP_CMA, vec = strategy == ES_STRAT_PGPE || strategy == ES_STRAT_SNES;
     const int32_t P64 = (g.P + 63) / 64 * 64;
     e.wg = P64 < EVAL_MAX_WG ? P64 : EVAL_MAX_WG;
     e.n_pg = (g.P + e.wg - 1) / e.wg;
     const int64_t waves_per_chunk = (int64_t)e.n_pg * (e.wg / 64) * g.R;
     const bool large = (int64_t)g.P * g.nb > EVAL_LARGE_FROM;
     const double pair_blocks = (double)g.R * g.P * g.nb, wave_blocks = (double)waves_per_chunk * g.nb;
-    // One launch for evaluate and reduction while the second launch, its chain
-    // of loads and the chunks' start-ups cost more than a workgroup of one or a
-    // few pairs does: for a run of its own plan up to 6e6 pair-blocks, more
-    // where the other kernels leave lanes idle (fewer than 64 pairs, squared by
-    // the share), with at least 96 workgroups.  Evaluate in us, two launches /
-    // one (sphere, Rastrigin): 1000 dims x 256 members 5.8 / 3.7, 6.0 / 4.2;
-    // 100 x 64 x 1024 runs 10.6 / 5.3, 12.5 / 6.3; 20,000 x 256 9.3 / 6.9, 11.1 /
-    // 8.2; 10,007 x 1024 x 2 12.3 / 9.4, 14.8 / 11.9; 50,001 x 510 15.1 / 12.3,
-    // 18.7 / 16.0; 40,528 x 1096 (5.6e6) 22.2 / 20.2, 28.4 / 28.1; 20,000 x 1000 x 4
-    // (1.0e7) 27.0 / 24.9, 34.5 / 34.8; 100,001 x 510 x 2 (1.3e7) 32.2 / 31.8, 42.1 /
-    // 45.2; with half the lanes idle 200,000 x 64 x 8 (1.3e7) 52.6 / 47.3, 72.7 /
-    // 61.0; 60,000 x 64 (32 workgroups) 11.9 / 13.3, 13.1 / 18.0.  Independent
-    // members take twice the noise and registers: one launch only for the runs
-    // of the smaller plan (10,007 x 1024 x 2 20.0 / 23.2, 50,001 x 510 25.9 / 32.3).
-    const double spread = wave_blocks * 64.0 / pair_blocks;
-    e.small = !large || (!indep && pair_blocks <= 6e6 * spread * spread && (int64_t)g.R * g.P >= 96);
-    // Even and odd sums save VALU instructions and cost a staged tile per
-    // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, members /
-    // folded at their best chunks, shifted sphere: 36,000 12.7 / 14.1; 40,032
-    // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
-    // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
-    e.folded = !e.small && !indep && large && g.P >= 2 && wave_blocks >= 65536.0;
-    int64_t bc, ref_chunks = 0;
-    if (bc_override > 0) {
-        bc = bc_override;
-    } else {
+    int64_t bc = bc_override, ref_chunks = 0;
+    if (bc_override <= 0) {
         // About 24576 waves over the launch (three rounds of a full chip at
         // 8 waves per SIMD), with at least EVAL_FOLD blocks per chunk: the
         // shorter workgroups of three rounds leave a shorter tail while the
@@ -2839,10 +2838,7 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
         if (nch < 1) nch = 1;
         bc = (g.nb + nch - 1) / nch;
         if (bc < EVAL_FOLD) bc = EVAL_FOLD;
-        if (large) {
-            ref_chunks = (g.nb + bc - 1) / bc;
-            bc = e.small ? std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD) : eval_chunk_blocks(g, e, ref_chunks, indep);
-        }
+        if (large) ref_chunks = (g.nb + bc - 1) / bc;
         // a small run: chunks short enough that the fused loop's workgroup
         // takes every (pair, chunk) item at once
         if ((int64_t)g.P * g.nb <= (int64_t)FUSED_WG * EVAL_FOLD) {
@@ -2852,9 +2848,44 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, bool indep)
         }
     }
     if (bc > g.nb) bc = g.nb;
+    // One launch for evaluate and reduction while the second launch, its chain
+    // of loads and the chunks' start-ups cost more than a workgroup of one or a
+    // few pairs does.  A run of the smaller plan (chunks 1 to 7 on as many XCDs
+    // in two launches): wherever it pays by wave-blocks.  A run of its own plan:
+    // up to 6e6 pair-blocks besides, more where the other kernels leave lanes idle
+    // (fewer than 64 pairs, squared by the share), with at least 96 workgroups.
+    // Evaluate in us, two launches / one (sphere, Rastrigin): 1000 dims x 256
+    // members 5.8 / 3.7, 6.0 / 4.2; 100 x 64 x 1024 runs 10.6 / 5.3, 12.5 / 6.3;
+    // 20,000 x 256 9.3 / 6.9, 11.1 / 8.2; 10,007 x 1024 x 2 12.3 / 9.4, 14.8 / 11.9;
+    // 50,001 x 510 15.1 / 12.3, 18.7 / 16.0; 40,528 x 1096 (5.6e6) 22.2 / 20.2, 28.4 /
+    // 28.1; 20,000 x 1000 x 4 (1.0e7) 27.0 / 24.9, 34.5 / 34.8; 100,001 x 510 x 2
+    // (1.3e7) 32.2 / 31.8, 42.1 / 45.2; with half the lanes idle 200,000 x 64 x 8
+    // (1.3e7) 52.6 / 47.3, 72.7 / 61.0; 60,000 x 64 (32 workgroups) 11.9 / 13.3, 13.1 /
+    // 18.0.  With a sigma for every dim each lane reads a third row at a place of its
+    // own: up to 1.5e6 pair-blocks (shifted sphere, Rosenbrock: 10,007 x 1024 (1.3e6)
+    // 14.7 / 13.1, 16.1 / 12.6; x 2 runs 15.5 / 21.9, 17.2 / 23.5; 50,835 x 86 x 13 34 /
+    // 58, 41 / 80).  Independent members take twice the noise and registers: one
+    // launch only for the runs of the smaller plan (10,007 x 1024 x 2 20.0 / 23.2,
+    // 50,001 x 510 25.9 / 32.3).
+    const double spread = wave_blocks * 64.0 / pair_blocks;
+    if (!large) {
+        const int64_t nch = (g.nb + bc - 1) / bc;
+        e.small = one_launch_pays(g, bc, nch, wave_blocks * (double)((nch + 7) / 8 * 8) / (double)nch);
+    } else {
+        const int64_t bs = bc_override > 0 ? bc : std::max<int64_t>((g.nb + SMALL_WG - 1) / SMALL_WG, EVAL_FOLD);
+        e.small = !indep && pair_blocks <= (vec ? 1.5e6 : 6e6) * spread * spread && (int64_t)g.R * g.P >= 96 &&
+                  one_launch_pays(g, bs, (g.nb + bs - 1) / bs, wave_blocks);
+        if (e.small) bc = bs;
+    }
+    // Even and odd sums save VALU instructions and cost a staged tile per
+    // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, members /
+    // folded at their best chunks, shifted sphere: 36,000 12.7 / 14.1; 40,032
+    // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
+    // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
+    e.folded = !e.small && !indep && large && g.P >= 2 && wave_blocks >= 65536.0;
+    if (large && !e.small && bc_override <= 0) bc = std::min(eval_chunk_blocks(g, e, ref_chunks, indep), g.nb);
     e.bc = bc;
     e.nchunks = (g.nb + bc - 1) / bc;
-    e.small = e.small && e.nchunks <= SMALL_MAX_CHUNKS;  // its partials in LDS, at most four passes over the chunks
     // At least what the smaller runs' plan takes, so that the static scratch
     // holds the same evaluates under either (one launch uses none of it).
     e.partial_chunks = ref_chunks > 0 && e.small ? ref_chunks : std::max(ref_chunks, e.nchunks);
@@ -2937,7 +2968,7 @@ hipError_t launch_eval_bbob(const Geometry& g, const es_config& c, const EvalPla
     const double add = c.problem == ES_PROB_RASTRIGIN ? (double)c.rastrigin_a * (double)g.D : 0.0;
     if (e.small) {
         const int sm = c.strategy == ES_STRAT_SEP_CMA ? SM_INDEP : svec ? SM_VEC : SM_SCALAR;
-        const int32_t pw = std::max(1, std::min(std::min(SMALL_WG / (int32_t)e.nchunks, SMALL_MAX_PAIRS), g.P));
+        const int32_t pw = small_pairs(g, e.nchunks);
         const dim3 sgrid((unsigned)((g.P + pw - 1) / pw), (unsigned)g.R);
         const uint32_t lds = (uint32_t)(2 * pw * (sizeof(double) * RED_SLICES + sizeof(float) * e.nchunks));
 #define ES_SMALL(PROB, SM)                                                                                             \

@@ -15,7 +15,14 @@ def _path(D, N, R=1, bc=0, problem=P.PROB_SPHERE, **kw):
 @pytest.mark.parametrize("D,N,R,strategy,path", [
     (16, 32, 1, P.STRAT_OPENAI_ES, 1), (1000, 256, 1, P.STRAT_PGPE, 1), (100, 64, 1024, P.STRAT_SEP_CMA, 1),
     (131075, 130, 1, P.STRAT_OPENAI_ES, 3), (131075, 130, 1, P.STRAT_SNES, 3), (131075, 130, 1, P.STRAT_SEP_CMA, 2),
-    (1_000_000, 2048, 1, P.STRAT_OPENAI_ES, 3), (2_000_000, 2, 1, P.STRAT_OPENAI_ES, 2)])
+    (1_000_000, 2048, 1, P.STRAT_OPENAI_ES, 3), (2_000_000, 2, 1, P.STRAT_OPENAI_ES, 2),
+    # one launch where it pays: many runs of full workgroups, but not of half-empty ones, of more than two passes
+    # over the chunks, or of a third row a lane
+    (1000, 256, 1000, P.STRAT_OPENAI_ES, 1), (2000, 512, 64, P.STRAT_SNES, 1), (4000, 512, 32, P.STRAT_OPENAI_ES, 2),
+    (4000, 128, 128, P.STRAT_SEP_CMA, 2), (2100, 512, 8, P.STRAT_OPENAI_ES, 1), (2100, 512, 32, P.STRAT_OPENAI_ES, 2),
+    (8192, 64, 1, P.STRAT_OPENAI_ES, 1), (9000, 64, 1, P.STRAT_OPENAI_ES, 2), (16384, 128, 1, P.STRAT_SEP_CMA, 2),
+    (10007, 1024, 1, P.STRAT_PGPE, 1), (10007, 1024, 2, P.STRAT_PGPE, 2), (10007, 1024, 2, P.STRAT_OPENAI_ES, 1),
+    (2100, 1000, 16, P.STRAT_OPENAI_ES, 3)])
 def test_kernel_of_a_configuration(D, N, R, strategy, path):
     got, partials = _path(D, N, R, strategy=strategy)
     assert got == path
