@@ -258,8 +258,9 @@ es_status es_eval(es_handle* h, float* fitness_out);
  * (hipEvent_t handles the caller created with timing enabled; either may be
  * NULL) are recorded by that kernel's dispatch itself (hipExtLaunchKernel),
  * at its start and at its end, so the stream carries no marker packet.  The
- * main kernel is the fused sample + evaluate (the benchmark problems; the
- * per-chunk sums are reduced by a second kernel after it) or the MLP forward
+ * main kernel is the fused sample + evaluate (the benchmark problems; with
+ * es_eval_path 1 it also reduces the per-chunk sums, else a second kernel does
+ * that after it, outside the events) or the MLP forward
  * (a teacher kernel, when one runs, goes before it).  hipEventElapsedTime of
  * the two gives that kernel's time.  Same results as es_eval.  A timing
  * aid: not meant for a stream under capture. */
@@ -283,9 +284,10 @@ es_status es_eval_timed(es_handle* h, float* fitness_out, void* start_event, voi
  *   fitness       device [R][N] output, the same bits es_eval gives a handle
  *                 with this config, mean, sigma and t
  *   hip_stream    hipStream_t the kernels are enqueued on (NULL: default)
- * ES_ERR_ARG when the evaluate's partial sums need more than 16 MiB (the
- * default plan needs about 12.6 MB for any run count and population; a
- * small cfg.plan_eval_blocks can need more).  Errors are reported through
+ * ES_ERR_ARG when the evaluate's partial sums in two launches take more than
+ * 16 MiB, also where it runs in one launch that keeps none (the default plan
+ * stays within it up to about a million members over all runs, whatever the
+ * dimension; a small cfg.plan_eval_blocks can take more).  Errors are reported through
  * es_last_error(NULL).  Calls that overlap on one device (several streams or
  * threads) share the array and race: serialise them. */
 es_status es_eval_noalloc(const es_config* cfg, const float* mean, const float* problem_data, const float* sigma,

@@ -510,7 +510,7 @@ int32_t es_eval_path(const es_config* cfg, int64_t* partial_floats)
     if (cfg->problem == ES_PROB_MLP) return 4;
     const Geometry g = geometry_of(*cfg);
     const EvalPlan e = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy);
-    if (partial_floats) *partial_floats = e.small ? 0 : e.nchunks * g.R * (int64_t)g.N;
+    if (partial_floats) *partial_floats = eval_partial_elems(g, e);
     return e.small ? 1 : e.folded ? 3 : 2;
 }
 
@@ -712,10 +712,11 @@ es_status es_eval_noalloc(const es_config* cfg, const float* mean, const float* 
     if (t < 0 || t > 0xFFFFFFFFll) return init_fail(ES_ERR_ARG, "t out of range", kNoalloc);
     const Geometry g = geometry_of(*cfg);
     const EvalPlan plan = eval_plan(g, cfg->plan_eval_blocks, cfg->strategy);
-    const int64_t need = eval_partial_elems(g, plan);
+    const int64_t need = plan.scratch_chunks * g.R * (int64_t)g.N;
     if (need > (int64_t)NOALLOC_SCRATCH_FLOATS) {
         std::snprintf(g_init_err, sizeof(g_init_err),
-                      "es_eval_noalloc: this evaluate needs %lld bytes of partial sums; the static scratch holds %zu",
+                      "es_eval_noalloc: this evaluate takes %lld bytes of partial sums in two launches; the static scratch "
+                      "holds %zu",
                       (long long)need * 4, NOALLOC_SCRATCH_FLOATS * 4);
         return ES_ERR_ARG;
     }

@@ -44,7 +44,7 @@ struct EvalPlan {
     int32_t n_pg;     // pair groups per run
     int64_t bc;       // blocks per chunk
     int64_t nchunks;  // chunks per member
-    int64_t partial_chunks;  // chunks that a partials buffer has room for
+    int64_t scratch_chunks;  // chunks that the static scratch must have room for
     bool small;       // one launch (k_eval_small) instead of evaluate and reduction
     bool folded;      // even and odd sums of a pair (k_eval_fold) instead of its two members
 };
@@ -54,7 +54,7 @@ struct EvalPlan {
 // loops' order.
 constexpr int64_t EVAL_LARGE_FROM = 1 << 18;
 EvalPlan eval_plan(const Geometry& g, int64_t bc_override, int32_t strategy);
-int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e);  // floats
+int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e);  // floats between two launches (0: one launch)
 
 hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m1, float* v,
                        float* best_x, hipStream_t s);

@@ -2886,13 +2886,13 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, int32_t strategy)
     if (large && !e.small && bc_override <= 0) bc = std::min(eval_chunk_blocks(g, e, ref_chunks, indep), g.nb);
     e.bc = bc;
     e.nchunks = (g.nb + bc - 1) / bc;
-    // At least what the smaller runs' plan takes, so that the static scratch
-    // holds the same evaluates under either (one launch uses none of it).
-    e.partial_chunks = ref_chunks > 0 && e.small ? ref_chunks : std::max(ref_chunks, e.nchunks);
+    // What es_eval_noalloc is held to: at least what the smaller runs' plan takes
+    // in two launches, so that it takes the same evaluates under every plan.
+    e.scratch_chunks = ref_chunks > 0 && e.small ? ref_chunks : std::max(ref_chunks, e.nchunks);
     return e;
 }
 
-int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e) { return e.partial_chunks * g.R * (int64_t)g.N; }
+int64_t eval_partial_elems(const Geometry& g, const EvalPlan& e) { return e.small ? 0 : e.nchunks * g.R * (int64_t)g.N; }
 
 hipError_t launch_init(const Geometry& g, const es_config& c, float* m, float* m1, float* v,
                        float* best_x, hipStream_t s)

@@ -1,9 +1,11 @@
 """The evaluate's kernels per configuration, from es_eval_path (CPU only: a host
 rule).  The sizes of the GPU tests that name a kernel are checked against it there."""
+import ctypes
 import math
 import random
 
 import pytest
+import torch
 
 import paper_2212_04180_amd as P
 
@@ -61,3 +63,14 @@ def test_partials_of_large_evaluates_are_bounded():
         _, partials = _path(D, N, R, strategy=rng.choice((P.STRAT_OPENAI_ES, P.STRAT_PGPE, P.STRAT_SEP_CMA)))
         if (N // 2) * nb > 1 << 18:
             assert partials <= max(-(-nb // bc) * R * N, 1 << 22), (D, N, R)
+
+
+@pytest.mark.parametrize("D,N,R,path", [(400, 66, 65535, 1), (4_000_000, 8_000_000, 1, 3)])
+@pytest.mark.skipif(torch.cuda.is_available(), reason="made-up pointers: only where nothing could run on them")
+def test_noalloc_is_held_to_two_launches(D, N, R, path):
+    # refused before any device work where two launches would not fit the static scratch, whichever path runs
+    cfg = P.ESConfig(num_dims=D, popsize=N, num_runs=R, problem=P.PROB_SPHERE)
+    assert P.eval_path(cfg)[0] == path
+    cs, p = cfg.cstruct(), ctypes.c_void_p(64)
+    assert P.lib().es_eval_noalloc(ctypes.byref(cs), p, None, p, 0, p, None) == -1
+    assert b"partial sums in two launches" in P.lib().es_last_error(None)

@@ -40,3 +40,15 @@ def test_handle_memory_of_many_members():
     es = P.ES(P.ESConfig(num_dims=45472, popsize=4474, num_runs=136, seed=5, problem=P.PROB_SPHERE))
     es.sync()
     assert free - torch.cuda.mem_get_info()[0] < 400 << 20
+
+
+def test_one_launch_keeps_no_partials():
+    # 20,003 dims x 2048 members in one launch: 10 MB of partial sums a handle if they were allocated
+    import paper_2212_04180_amd as P
+    cfg = P.ESConfig(num_dims=20003, popsize=2048, seed=5, problem=P.PROB_SPHERE)
+    assert P.eval_path(cfg) == (1, 0)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    handles = [P.ES(cfg) for _ in range(8)]
+    handles[-1].sync()
+    assert free - torch.cuda.mem_get_info()[0] < 8 * 6 << 20
