@@ -1412,9 +1412,14 @@ __device__ __forceinline__ TellRows tell_rows(const TellArgs& a, int64_t b, int3
     t.sigma = a.hp[r];
     t.lr = a.hp[a.R + r];
     t.jb = a.best_j[r];
+    // the first moments or the path, the second moments: Adam, Sep-CMA-ES and
+    // Adam only (SNES and ClipUp keep neither up)
+    const bool cma = a.strategy == ES_STRAT_SEP_CMA;
+    const bool adam = !cma && a.strategy != ES_STRAT_SNES && a.optimizer != ES_OPT_CLIPUP;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     t.m4 = *reinterpret_cast<const float4*>(a.m + off);
-    t.m14 = *reinterpret_cast<const float4*>(a.m1 + off);
-    t.v4 = *reinterpret_cast<const float4*>(a.v + off);
+    t.m14 = adam || cma ? *reinterpret_cast<const float4*>(a.m1 + off) : zero;
+    t.v4 = adam ? *reinterpret_cast<const float4*>(a.v + off) : zero;
     t.s4 = a.sig ? *reinterpret_cast<const float4*>(a.sig + off) : make_float4(t.sigma, t.sigma, t.sigma, t.sigma);
     return t;
 }
