@@ -1583,7 +1583,9 @@ __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
 
     double a64[4] = {0.0, 0.0, 0.0, 0.0}, b64[4] = {0.0, 0.0, 0.0, 0.0};
     TellRows rows{};
-    if (SUB > 1 && s == 0) rows = tell_rows(a, (int64_t)bb, r);
+    // one block's chain is all there is in small runs, with or without sub-slices
+    constexpr bool early = SUB > 1 || (!TWO && !UNIT);
+    if (early && s == 0 && a.nsplit == 1) rows = tell_rows(a, (int64_t)bb, r);
     if constexpr (ROWS)
         tell_slice2<LANES_BLOCK, true>(a.cw, a.cw, k0, k1, bb, a.t, pb, pe, a64, b64, a.elite + (int64_t)r * 2 * a.P);
     else if constexpr (TWO)
@@ -1624,7 +1626,7 @@ __global__ __launch_bounds__(TELL_LANES * TELL_MAX_PS) void k_tell(TellArgs a)
         return;
     }
     if (SUB > 1 && si != 0) return;  // SUB > 1 only where no per-wave norm partials are kept
-    if (SUB == 1 && b < a.nb) rows = tell_rows(a, b, r);
+    if (!early && b < a.nb) rows = tell_rows(a, b, r);
     const double g2 = b < a.nb ? tell_finish(a, rows, a64, b64, b, r, k0, k1) : 0.0;
     if (a.gpart) {
         const double tot = wave_sum(g2);
