@@ -38,16 +38,22 @@ def _both(cfg, m=None, sig=None):
     return es.eval().cpu().numpy(), ref.eval(), ref
 
 
-# (D, N, R, plan_eval_blocks): above 2^18 pair-blocks a run and 2^16 wave-blocks
-SIZES = [(16389, 510, 1, 0), (33334, 1026, 1, 7), (131075, 128, 2, 0), (16400, 512, 2, 3), (20003, 2048, 1, 700)]
+# (D, N, R, plan_eval_blocks), the path (es_eval_path) with one sigma and with one a dim: 3 is the kernel of the even
+# and odd sums (more than 2^18 pair-blocks a run and 2^16 wave-blocks, and no one-launch evaluate), the others are
+# large runs on either side of it
+SIZES = [((131075, 130, 1, 0), (3, 3)), ((131077, 94, 2, 0), (3, 3)), ((131075, 130, 1, 7), (3, 3)),
+         ((262149, 66, 1, 3), (3, 3)), ((23501, 2048, 1, 700), (3, 3)), ((59302, 1026, 1, 0), (3, 3)),
+         ((16389, 510, 1, 0), (1, 1)), ((33334, 1026, 1, 7), (3, 3)), ((131075, 128, 2, 0), (1, 3)),
+         ((16400, 512, 2, 3), (2, 2)), ((20003, 2048, 1, 700), (1, 3))]
 
 
 @pytest.mark.parametrize("strategy", ["openai", "pgpe"])
 @pytest.mark.parametrize("problem", ["sphere", "shifted_sphere", "rosenbrock", "rastrigin"])
 @pytest.mark.parametrize("size", range(len(SIZES)))
 def test_large_evaluate_matches_oracle(size, problem, strategy):
-    D, N, R, bc = SIZES[size]
+    (D, N, R, bc), paths = SIZES[size]
     cfg = _cfg(problem, D, N, R, strategy, bc)
+    assert _P().eval_path(cfg)[0] == paths[strategy == "pgpe"]
     sig = None
     if strategy == "pgpe":
         sig = np.random.default_rng(size).uniform(0.02, 0.2, (R, D)).astype(np.float32)
@@ -62,10 +68,12 @@ def test_large_evaluate_matches_oracle(size, problem, strategy):
             assert np.all(np.abs(f[r, j0:j0 + 256].astype(np.float64) - fr[r, j0:j0 + 256]) <= bound), (r, j0)
 
 
+@pytest.mark.parametrize("D,N,path", [(16389, 512, 1), (131075, 130, 3)])
 @pytest.mark.parametrize("problem", ["sphere", "shifted_sphere", "rosenbrock"])
-def test_members_near_the_optimum_keep_their_digits(problem):
+def test_members_near_the_optimum_keep_their_digits(problem, D, N, path):
     # pair 3's + member sits on the optimum: its even and odd sums cancel
-    cfg = _cfg(problem, 16389, 512, sigma=0.5)
+    cfg = _cfg(problem, D, N, sigma=0.5)
+    assert _P().eval_path(cfg)[0] == path
     oc = to_oracle(cfg)
     eps = O.normals(cfg.seed, O.DOM_NOISE, 3, 0, 0, cfg.num_dims)
     opt = O.problem_data(oc) if problem == "shifted_sphere" else np.float32(1.0 if problem == "rosenbrock" else 0.0)
@@ -74,18 +82,20 @@ def test_members_near_the_optimum_keep_their_digits(problem):
     pdata = O.problem_data(oc) if problem == "shifted_sphere" else None
     bound = stagecheck._fitness_bound(cfg, ref.ask()[0], np.float32(0.5), pdata)
     assert np.all(np.abs(f[0].astype(np.float64) - fr[0]) <= bound)
-    assert f[0, 3] <= fr[0, 3] + bound[3] and bound[3] < 1e-6 * f[0, 3 + 256]
+    assert f[0, 3] <= fr[0, 3] + bound[3] and bound[3] < 1e-6 * f[0, 3 + N // 2]
 
 
 @pytest.mark.parametrize("strategy", ["openai", "pgpe"])
 @pytest.mark.parametrize("problem", ["sphere", "shifted_sphere", "rosenbrock", "rastrigin"])
 @pytest.mark.parametrize("value", [1e19, 3e20, np.inf, np.nan])
-def test_overflow_and_nan_as_member_by_member(value, problem, strategy):
+@pytest.mark.parametrize("D,N,path", [(16389, 512, 1), (131075, 130, 3)])
+def test_overflow_and_nan_as_member_by_member(value, problem, strategy, D, N, path):
     # one dim of the mean is huge or not a number: the same infinities and NaN as the oracle's members
-    cfg = _cfg(problem, 16389, 512, strategy=strategy)
-    m = np.random.default_rng(1).uniform(-2, 2, (1, 16389)).astype(np.float32)
+    cfg = _cfg(problem, D, N, strategy=strategy)
+    assert _P().eval_path(cfg)[0] == path
+    m = np.random.default_rng(1).uniform(-2, 2, (1, D)).astype(np.float32)
     m[0, 9001] = value
-    sig = np.full((1, 16389), 0.1, np.float32) if strategy == "pgpe" else None
+    sig = np.full((1, D), 0.1, np.float32) if strategy == "pgpe" else None
     with np.errstate(over="ignore", invalid="ignore"):
         f, fr, _ = _both(cfg, m, sig)
         fr = fr.astype(np.float32)

@@ -19,6 +19,7 @@ def test_noalloc_takes_many_runs(D, N, R):
     import paper_2212_04180_amd as P
     cfg = P.ESConfig(num_dims=D, popsize=N, num_runs=R, sigma=0.1, seed=5, init_lo=-2.0, init_hi=2.0,
                      problem=P.PROB_SPHERE)
+    assert P.eval_path(cfg)[0] == 3
     es = P.ES(cfg)
     mean = es.get_state()["m"]
     es.ask()
