@@ -47,12 +47,18 @@ MLP_FLOPS_PER_MEMBER = 2 * 256 * (64 * 256 + 256 * 256 + 256 * 16)
 PHILOX_BM = 60 + 46
 EVAL_SLOTS_PER_PAIR_BLOCK = {"sphere": PHILOX_BM + 24, "shifted_sphere": PHILOX_BM + 32,
                              "rosenbrock": PHILOX_BM + 64, "rastrigin": PHILOX_BM + 80}
-# Large evaluates with antithetic pairs and one sigma a run keep a pair's even
-# and odd sums (k_eval_fold): Philox and the four shifts, scales and eight
+# Large evaluates with antithetic pairs keep a pair's even and odd sums
+# (k_eval_fold, es_eval_path 3): Philox and the four shifts, scales and eight
 # transcendentals (100), then per block and with the fp64 folds and the row
 # sums (2): sphere 2 x (add, mul, 2 fma); Rosenbrock 2 x (mul, fma) + 4 x 7;
-# Rastrigin 2 x (mul, fma) + 4 x (mul, fract, sin (4), cos (4), 3 fma).
+# Rastrigin 2 x (mul, fma) + 4 x (mul, fract, sin (4), cos (4), 3 fma).  With a
+# sigma for every dim, per dim: sphere 2 mul, 2 fma; Rosenbrock 3 mul, 7 fma;
+# Rastrigin 2 mul, fma, fract, sin (4), cos (4), 3 fma.
 FOLD_SLOTS_PER_PAIR_BLOCK = {"sphere": 110, "shifted_sphere": 110, "rosenbrock": 134, "rastrigin": 158}
+FOLD_VEC_SLOTS_PER_PAIR_BLOCK = {"sphere": 118, "shifted_sphere": 118, "rosenbrock": 142, "rastrigin": 162}
+EVAL_KERNELS = {1: "k_eval_small (fused sample+evaluate and its reduction)",
+                2: "k_eval_bbob (fused sample+evaluate)",
+                3: "k_eval_fold (fused sample+evaluate, a pair's even and odd sums)"}
 # tell: Philox + Box-Muller + 4 fma (w * eps) + the fp64 fold every 16 pairs;
 # large runs' single sum weighs the radius instead of the normals (4 fewer)
 TELL_SLOTS_PER_PAIR_BLOCK = PHILOX_BM + 4 + 1
@@ -67,6 +73,18 @@ RUN_PATHS = {1: "per-call kernels", 2: "fused loop (k_run_fused, one workgroup p
 # VGPR (4 movs per block); tell adds the second sum, 4 fma (z*z - 1) + 4 fma
 EVAL_VEC_EXTRA = 4
 TELL_TWO_EXTRA = 8
+
+
+def eval_slots_and_kernel(P, cfg, prob):
+    """Algorithmic slots per pair-block of the evaluate that the library runs
+    for cfg, and that kernel's name."""
+    path = P.eval_path(cfg)[0]
+    vec = cfg.strategy != P.STRAT_OPENAI_ES
+    if path == 3:
+        return (FOLD_VEC_SLOTS_PER_PAIR_BLOCK if vec else FOLD_SLOTS_PER_PAIR_BLOCK)[prob], EVAL_KERNELS[path]
+    slots = EVAL_SLOTS_PER_PAIR_BLOCK[prob] + (EVAL_VEC_EXTRA if vec else 0)
+    # independent members: a second Philox block and Box-Muller per pair-block
+    return slots + (PHILOX_BM if cfg.strategy == P.STRAT_SEP_CMA else 0), EVAL_KERNELS[path]
 
 
 def kernel_source_sha256():
@@ -266,17 +284,12 @@ def time_workload(P, torch, name, K, W, path, dev, stream, copy_mib=0):
     roof = None
     if prob is not None and path == "percall":
         vec = cfg.strategy != P.STRAT_OPENAI_ES
-        eval_slots = EVAL_SLOTS_PER_PAIR_BLOCK[prob] + (EVAL_VEC_EXTRA if vec else 0)
+        eval_slots, eval_kernel = eval_slots_and_kernel(P, cfg, prob)
         large = (N // 2) * ((D + 3) // 4) > LARGE_FROM
-        folded = large and not vec and pair_blocks >= 65536 * 64 and N >= 128 and pair_blocks > 6e6
-        if folded:
-            eval_slots = FOLD_SLOTS_PER_PAIR_BLOCK[prob]
         tell_slots = TELL_SLOTS_PER_PAIR_BLOCK + (TELL_TWO_EXTRA if vec else -TELL_LARGE_SAVES if large else 0)
         tell_items = pair_blocks
         if cfg.strategy == P.STRAT_SEP_CMA:
-            # independent members: a second Philox block and Box-Muller per
-            # pair-block; the gradient sums run over the mu elites
-            eval_slots += PHILOX_BM
+            # the gradient sums run over the mu elites
             mu = max(1, int(cfg.elite_ratio * N))
             tell_items = R * mu * ((D + 3) // 4)
         achieved = pair_blocks * eval_slots / (eval_ms * 1e-3)
@@ -287,8 +300,7 @@ def time_workload(P, torch, name, K, W, path, dev, stream, copy_mib=0):
                 "unit": "T VALU lane-op slots/s", "frac": achieved / VALU_PEAK,
                 "traffic": profiled_traffic(name),
                 "traffic_copy_scaled": profiled_traffic(name, "eval_hbm_bytes_per_launch"),
-                "kernel": "k_eval_fold (fused sample+evaluate, a pair's even and odd sums)" if folded
-                          else "k_eval_bbob or k_eval_small (fused sample+evaluate)",
+                "kernel": eval_kernel,
                 "kernel_ms": eval_ms, "slots_per_pair_block": eval_slots,
                 "pair_blocks_per_launch": pair_blocks,
                 "issued_instructions_per_pair_block": issued,

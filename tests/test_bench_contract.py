@@ -42,3 +42,18 @@ def test_other_workloads_are_the_remaining_four():
     for name, (path, K, W) in bench.OTHER_WORKLOADS.items():
         workloads.get(name)
         assert path in ("percall", "run") and K > 0 and W >= 0
+
+
+def test_evaluate_slots_are_those_of_the_kernel_that_runs():
+    import bench
+    import paper_2212_04180_amd as P
+    def slots(D, N, **kw):
+        cfg = P.ESConfig(num_dims=D, popsize=N, problem=P.PROB_SHIFTED_SPHERE, **kw)
+        return bench.eval_slots_and_kernel(P, cfg, "shifted_sphere")
+    for strategy, large, small in ((P.STRAT_OPENAI_ES, 110, 138), (P.STRAT_PGPE, 118, 142), (P.STRAT_SNES, 118, 142)):
+        n, kernel = slots(1_000_000, 2048, strategy=strategy)
+        assert n == large and kernel.startswith("k_eval_fold ")
+        n, kernel = slots(1000, 256, strategy=strategy)
+        assert n == small and kernel.startswith("k_eval_small ")
+    n, kernel = slots(1_000_000, 2048, strategy=P.STRAT_SEP_CMA)
+    assert n == 142 + 106 and kernel.startswith("k_eval_bbob ")
