@@ -8,7 +8,9 @@
 //   k_eval_bbob       fused sample + evaluate (Sec. 2.1 evaluate) for the
 //                     benchmark problems; lane = antithetic pair (or member
 //                     pair for independent sampling), D chunked
+//   k_eval_fold       the same for large runs, by a pair's even and odd sums
 //   k_eval_reduce     fixed-order sum of the per-chunk partials -> fitness
+//   k_eval_small      evaluate and reduction in one launch
 //   k_rank            fitness shaping (Sec. 3.2): centered ranks with index
 //                     tie-break, raw keys, z-scores, weight decay, the rank
 //                     tables of SNES and Sep-CMA-ES; antithetic fold,
@@ -18,11 +20,12 @@
 //                     with the strategy's update; lane = a block of four dims;
 //                     for the MLP problem its launch also runs the next
 //                     generation's teacher rows (es_teacher.hpp)
-//   k_tell_fold       the split gradient's partial sums in split order, then
-//                     the update
+//   k_tell_fold, k_tell_fold_many       the split gradient's partial sums in
+//                     split order or by slices, then the update
 //   k_clipup_velocity, k_clipup_apply   ClipUp's two norm passes
 //   k_sepcma_finish, k_cma_scale        Sep-CMA-ES second pass, sampling scale
 //   k_run_fused       T whole generations in one launch for small runs
+//   k_export_rows     state arrays out of their padded rows
 //   k_debug_noise     raw words and normals of one stream (diagnostics)
 //
 // Every reduction runs in a fixed order (no floating-point atomics), so a
@@ -424,8 +427,11 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
 // What depends on the dim alone (a, cos 2 pi m, ...) is made once per
 // workgroup into LDS and read as broadcasts, so the loop spends its VALU
 // instructions on one even and one odd sum instead of on two members: per
-// Philox block 79 -> 58 (shifted sphere), 109 -> 82 (Rastrigin).  The kernel
-// is bound by their number.
+// Philox block 79 -> 61 (shifted sphere), 109 -> 84 (Rastrigin), counted with the
+// staging.  The kernel is bound by their number.  It keeps its eight waves per
+// SIMD by spilling up to 12 registers around its loop (none in it): the shifted
+// sphere's 7 are most of the 7 MB that its D = 1e6 launch writes beyond the
+// partials.
 //
 // The sums are fp32 over EVAL_FOLD blocks folded into fp64; the members'
 // values even + odd, even - odd are formed in fp64.  Where a lane's odd sum
@@ -2885,10 +2891,12 @@ EvalPlan eval_plan(const Geometry& g, int64_t bc_override, int32_t strategy)
         if (e.small) bc = bs;
     }
     // Even and odd sums save VALU instructions and cost a staged tile per
-    // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, members /
+    // workgroup: ahead from about 2^16 wave-blocks (evaluate in us, k_eval_bbob /
     // folded at their best chunks, shifted sphere: 36,000 12.7 / 14.1; 40,032
     // 14.0 / 14.4; 50,004 16.8 / 15.9; 72,000 17.4 / 17.4; 91,188 25.4 / 24.2;
-    // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).
+    // 160,000 30.9 / 28.2; 500,000 80.0 / 66.3; 4,000,000 525 / 409).  Full waves
+    // with one sigma are in one launch up to 93,750; the line is for fewer than 96
+    // pairs, for a sigma a dim, and where one launch does not pay.
     e.folded = !e.small && !indep && large && g.P >= 2 && wave_blocks >= 65536.0;
     if (large && !e.small && bc_override <= 0) bc = std::min(eval_chunk_blocks(g, e, ref_chunks, indep), g.nb);
     e.bc = bc;
