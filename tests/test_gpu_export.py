@@ -91,3 +91,27 @@ def test_weights_and_ranks_out(N, R):
     assert np.all(got[:, 0] == -9) and np.all(got[:, 1 + N * R:] == -9)
     for r in range(R):
         np.testing.assert_array_equal(np.sort(got[1, 1 + r * N:1 + (r + 1) * N]), np.arange(N))
+
+
+def test_captured_readout_follows_the_state():
+    # es_get_state and es_get_strategy_state in a graph: every replay reads the state of its time
+    import paper_2212_04180_amd as P
+    s = torch.cuda.Stream()
+    es = P.ES(P.ESConfig(num_dims=1027, popsize=6, num_runs=3, seed=3, problem=P.PROB_SPHERE, strategy=P.STRAT_PGPE), stream=s)
+    out = torch.zeros(4, 3, 1027, device="cuda")
+    at = [ctypes.c_void_p(o.data_ptr()) for o in out]
+    L = P.lib()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        es._check(L.es_get_state(es._h, *at[:3], None))
+        es._check(L.es_get_strategy_state(es._h, at[3], None))
+    for k in range(4):
+        with torch.cuda.stream(s):
+            src = [torch.randn(3, 1027, device="cuda") for _ in range(3)] + [torch.rand(3, 1027, device="cuda")]
+            es.set_state(*src[:3], k)
+            es.set_strategy_state(src[3])
+            g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, src):
+            assert torch.equal(a, b), k
