@@ -421,16 +421,18 @@ bool kernel_can_store(const es_handle* h, void* p, size_t bytes)
 }
 
 // Several state arrays out (entries with a null dst are skipped): one launch
-// for all of them, or a copy command each where a destination is not plain
-// memory of the handle's device with room for its array or two of them overlap
-// (the last one then stays, as copies in order leave it).
+// for all of them, or a copy command each where the handle's device is not the
+// current one, a destination is not plain memory of it with room for its array,
+// or two of them overlap (the last one then stays, as copies in order leave it).
 es_status copy_out(es_handle* h, int64_t rows, int64_t D, std::initializer_list<std::pair<float*, const float*>> arrays)
 {
     float* dst[EXPORT_MAX];
     const float* src[EXPORT_MAX];
     const size_t bytes = (size_t)rows * (size_t)D * 4;
-    int n = 0;
-    bool kernel = true;
+    int n = 0, cur = -1;
+    // a kernel runs on the current device's queue where the handle has the
+    // default stream; a copy command finds its device by the addresses
+    bool kernel = hipGetDevice(&cur) == hipSuccess && cur == h->device;
     for (const auto& a : arrays) {
         if (!a.first) continue;
         dst[n] = a.first;

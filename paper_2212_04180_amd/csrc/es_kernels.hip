@@ -451,9 +451,10 @@ __global__ __launch_bounds__(EVAL_MAX_WG) __attribute__((amdgpu_waves_per_eu(8, 
 // chunk goes member by member; the workgroup sees that from the staged rows,
 // before its first block, and so does not work twice.  Without this the fitness
 // was off by 5e-4 at 1e-6 from the shifted sphere's optimum; it costs 1 to 4% of the
-// kernel (shifted sphere D = 1e6: 812 -> 818 us per generation).  Rastrigin's
-// A cos terms have larger roundings of their own, and the sphere's dims are its
-// members': neither needs it.
+// kernel (shifted sphere D = 1e6: 812 -> 818 us per generation).  Neither of the
+// others needs it: the sphere's terms are at most 2^-23 off by their own members'
+// roundings, Rastrigin's sum A D by 2^-22.5 |x| / sqrt(D) of it, below fp32 for
+// |x| up to a third of sqrt(D) (where A is not below x^2; else as the sphere).
 constexpr int FOLD_TILE_MIN = 256;  // dims staged at once, at least (else one per lane)
 
 template <int PROB, int SM>
