@@ -2776,7 +2776,8 @@ int grid_for(int64_t n, int threads)
 // ceil(chunks / 8) of them (11 chunks keep five of eight XCDs half idle: 8200
 // dims x 410 members x 186 runs 255 us, at 24 chunks 171), and a workgroup of
 // two waves sits on one SIMD (1e6 x 256 x 2 runs: 138 us at 14 workgroups a CU,
-// 126 at 12 and at 16).  Evaluate with its
+// 126 at 12 and at 16); those of three waves leave one SIMD a wave more
+// (independent members in 14,575 x 268 x 28: 114 us at 8 a CU, 96 at 17).  Evaluate with its
 // reduction in us, at 24576 waves (the smaller runs' plan) / at this rule's chunk,
 // shifted sphere: 50,001 dims x 510 members x 4 runs 45 / 34, 250,003 x 1000 88 /
 // 70, 1e6 x 2048 530 / 411, 1100 x 4096 x 100 151 / 131, 8200 x 410 x 186 262 / 201,
@@ -2799,10 +2800,12 @@ static int64_t eval_chunk_blocks(const Geometry& g, const EvalPlan& e, int64_t r
         const int64_t nch = (g.nb + bc - 1) / bc;
         if (nch > most) continue;  // one chunk (bc >= nb) never is
         const int64_t k = ((nch + 7) / 8 * per_chunk + 31) / 32;  // workgroups on the fullest CU
-        const int64_t on_simd = waves == 2 ? (k + 3) / 4 * 2 : k < 3 ? k * ((waves + 3) / 4) : (k * waves + 3) / 4;
+        const int64_t on_simd = waves == 2 ? (k + 3) / 4 * 2
+                                : k < 3    ? k * ((waves + 3) / 4)
+                                           : (k * waves + 3) / 4 + (waves == 3 && k >= 8 ? 1 : 0);
         const double per_simd = (double)on_simd;
         const double busy = block_us * (per_simd * ((double)bc + start) * (1.0 + 0.4 / std::min(per_simd, 8.0)) +
-                                        0.8 * (double)bc / (double)k);
+                                        0.65 * (double)bc / (double)k);
         const double us = std::max(busy, 1.5 * block_us * (double)bc) + (double)nch * (0.0042 + 1.6e-6 * (double)members);
         if (us < least) {
             least = us;
